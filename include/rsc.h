@@ -110,7 +110,8 @@ rsc_status_t rsc_csr_validate(const rsc_csr_t *A, int64_t *bad_row_host, hipStre
  * holds d; wider d in 64-float passes); when that slice of the referenced B
  * rows spans 2..16 ranges of about 4.5 MiB and rows hold at least 56, 112 or
  * 224 entries per range on average (64-, 32-, 16-float passes), the columns
- * are cut into P = min(8, ranges) equal index ranges processed one after
+ * are cut into P = min(8, ranges) equal index ranges (64-float passes: of
+ * about 3 MiB, up to 12, while a row keeps 56 entries per range) processed one after
  * another (the gathered B rows then stay in L2, or mostly so for ranges of
  * up to two L2 sizes); each row's entries in one range are summed as above and rounded
  * to an fp32 partial, and the P partials are added in fp64 in range order
@@ -128,7 +129,7 @@ rsc_status_t rsc_spmm(const rsc_csr_t *A, const float *B, int32_t d, int64_t ldb
  * same product with no workspace argument and no allocation. Its scratch is
  * a static 32 MiB device array inside the library, one per GPU, held until
  * the process ends; a product needs 512 bytes plus 4 max(n_rows,
- * min(8 n_rows, nnz / 1025)) bytes of it (about 8.3M rows at most), beyond
+ * min(12 n_rows, nnz / 1025)) bytes of it (about 8.3M rows at most), beyond
  * which the call returns RSC_ERR_CAPACITY without launching. A product whose
  * column-blocked buffers do not also fit runs unblocked (then Y may differ
  * from rsc_spmm's within rounding; otherwise it is bitwise equal). Every

@@ -33,6 +33,7 @@
 //   * the per-call preparation (long-row list or row order, split bounds)
 //     can be done once by a plan or at a cache refresh and reused.
 #include <cstdlib>
+#include <utility>
 
 #include "rsc_internal.h"
 
@@ -116,24 +117,21 @@ struct Layout {
     static_assert(kWave % LPE == 0, "LPE must divide the wave");
 };
 
+// ---- one entry per load instruction (LPE = 64) ----------------------------
 // Accumulates runs of 64 entries starting at beg, beg + stride, ... (< end)
 // into acc. `act[q]` says whether this lane's q-th float4 lies inside d.
-// Within a run, entry-group g takes entries g, g + G, g + 2G, ...; the group
-// partials are combined by a butterfly over the groups (fixed order, every
-// lane ends with the same sum) before the run is folded into fp64.
+// (col, val) are broadcast into SGPRs, so each B row has a scalar base.
 // Bit 31 of a column index is a cache hint (set by a plan or a cache on
 // their own copies; a caller's indices are < 2^31): with kHint, gathers of
 // columns without it bypass cache allocation (non-temporal), so the rows of
 // the columns that carry half the entries stay in L2. Values are unchanged.
-template <int LPE, int NV, bool kHint>
+template <int NV, bool kHint>
 __device__ __forceinline__ void accumulate_runs(const int32_t *__restrict__ col,
                                                 const float *__restrict__ val,
                                                 const float *__restrict__ B, int64_t ldb,
                                                 int64_t beg, int64_t end, int32_t stride,
                                                 const bool (&act)[NV], int lane,
                                                 double (&acc)[NV][4]) {
-    constexpr int G = Layout<LPE>::G;
-    const int g = lane / LPE, sl = lane % LPE;
     for (int64_t base = beg; base < end; base += stride) {  // int64: base + stride may pass 2^31 - 1
         const int32_t cnt = __builtin_amdgcn_readfirstlane((int32_t)min<int64_t>(kWave, end - base));
         int32_t my_c = 0;
@@ -145,86 +143,300 @@ __device__ __forceinline__ void accumulate_runs(const int32_t *__restrict__ col,
         float a[NV][4];
 #pragma unroll
         for (int q = 0; q < NV; ++q) a[q][0] = a[q][1] = a[q][2] = a[q][3] = 0.f;
-
-        if constexpr (G == 1) {
-            // one entry per instruction: broadcast (col, val) into SGPRs
-            for (int32_t t = 0; t < cnt; t += kUnroll) {
-                float4 b[kUnroll][NV];
-                float v[kUnroll];
+        for (int32_t t = 0; t < cnt; t += kUnroll) {
+            float4 b[kUnroll][NV];
+            float v[kUnroll];
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < kUnroll; ++u) {
 #pragma unroll
-                    for (int q = 0; q < NV; ++q) b[u][q] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    v[u] = 0.f;
-                    if (t + u < cnt) {  // wave-uniform
-                        const int32_t cf = __builtin_amdgcn_readlane(my_c, t + u);
-                        const int32_t c = cf & kColMask;
-                        v[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), t + u));
-                        const float4 *brow = reinterpret_cast<const float4 *>(B + (int64_t)c * ldb) + lane;
-                        if (kHint && cf >= 0) {  // not a hub column: stream it past the caches
-#pragma unroll
-                            for (int q = 0; q < NV; ++q)
-                                if (act[q]) b[u][q] = load_nt(brow + q * kWave);
-                        } else {
-#pragma unroll
-                            for (int q = 0; q < NV; ++q)
-                                if (act[q]) b[u][q] = brow[q * kWave];
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
-#pragma unroll
-                    for (int q = 0; q < NV; ++q) {
-                        a[q][0] = fmaf(v[u], b[u][q].x, a[q][0]);
-                        a[q][1] = fmaf(v[u], b[u][q].y, a[q][1]);
-                        a[q][2] = fmaf(v[u], b[u][q].z, a[q][2]);
-                        a[q][3] = fmaf(v[u], b[u][q].w, a[q][3]);
-                    }
-            }
-        } else {
-            static_assert(NV == 1, "sliced layouts hold one float4 per lane");
-            constexpr int kSteps = kWave / G;  // steps that cover the 64-entry run
-            constexpr int kWin = G >= 8 ? 4 : kUnroll;  // steps per window (gathers in flight)
-            // one window of kUnroll steps at a time: unrolling the step loop
-            // too keeps every window's (col, val) live at once (130 VGPRs for
-            // G = 2) and costs occupancy
-#pragma unroll 1
-            for (int t0 = 0; t0 < kSteps; t0 += kWin) {
-                if (t0 * G >= cnt) break;  // wave-uniform
-                float4 b[kWin];
-                float v[kWin];
-#pragma unroll
-                for (int u = 0; u < kWin; ++u) {
-                    const int j = (t0 + u) * G + g;  // entry of this group within the run
-                    const int32_t cf = __shfl(my_c, j & (kWave - 1));
+                for (int q = 0; q < NV; ++q) b[u][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                v[u] = 0.f;
+                if (t + u < cnt) {  // wave-uniform
+                    const int32_t cf = __builtin_amdgcn_readlane(my_c, t + u);
                     const int32_t c = cf & kColMask;
-                    const float vv = __shfl(my_v, j & (kWave - 1));
-                    b[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    v[u] = 0.f;
-                    if (t0 + u < kSteps && j < cnt && act[0]) {
-                        const float4 *brow = reinterpret_cast<const float4 *>(B + (int64_t)c * ldb) + sl;
-                        b[u] = (kHint && cf >= 0) ? load_nt(brow) : *brow;
-                        v[u] = vv;
-                    }
-                }
+                    v[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), t + u));
+                    const float4 *brow = reinterpret_cast<const float4 *>(B + (int64_t)c * ldb) + lane;
+                    if (kHint && cf >= 0) {  // not a hub column: stream it past the caches
 #pragma unroll
-                for (int u = 0; u < kWin; ++u) {
-                    a[0][0] = fmaf(v[u], b[u].x, a[0][0]);
-                    a[0][1] = fmaf(v[u], b[u].y, a[0][1]);
-                    a[0][2] = fmaf(v[u], b[u].z, a[0][2]);
-                    a[0][3] = fmaf(v[u], b[u].w, a[0][3]);
+                        for (int q = 0; q < NV; ++q)
+                            if (act[q]) b[u][q] = load_nt(brow + q * kWave);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < NV; ++q)
+                            if (act[q]) b[u][q] = brow[q * kWave];
+                    }
                 }
             }
 #pragma unroll
-            for (int m = LPE; m < kWave; m <<= 1)
+            for (int u = 0; u < kUnroll; ++u)
 #pragma unroll
-                for (int x = 0; x < 4; ++x) a[0][x] += __shfl_xor(a[0][x], m);
+                for (int q = 0; q < NV; ++q) {
+                    a[q][0] = fmaf(v[u], b[u][q].x, a[q][0]);
+                    a[q][1] = fmaf(v[u], b[u][q].y, a[q][1]);
+                    a[q][2] = fmaf(v[u], b[u][q].z, a[q][2]);
+                    a[q][3] = fmaf(v[u], b[u][q].w, a[q][3]);
+                }
         }
 #pragma unroll
         for (int q = 0; q < NV; ++q)
 #pragma unroll
             for (int x = 0; x < 4; ++x) acc[q][x] += (double)a[q][x];
+    }
+}
+
+// ---- G = 64 / LPE entries per load instruction (LPE = 4, 8, 16, 32) --------
+// Entry-group g (LPE lanes) takes entries g, g + G, g + 2G, ... of a 64-entry
+// run; its fp32 sum over them is folded into the lane's fp64 acc, and the
+// groups' sums are added when the row is done (sum_groups). Two forms give
+// the same sums bit for bit: through a buffer descriptor (accumulate_groups),
+// and with 64-bit addresses (accumulate_groups_wide) for operands that a
+// descriptor cannot cover and for the hub hint, which needs a lane mask
+// around two kinds of load (as two descriptor loads, each out of range for
+// the other's lanes, the hint gained less or lost: 1.86M nodes of mean
+// degree 26, d = 96, 2.89 ms against 2.52).
+//
+// The descriptor form: (col, val) are loaded in order and permuted once per
+// run, so that the entry group g needs at step t sits in a lane of g's own
+// row of 16 lanes and reaches the others by a DPP operand: entry t * G + g in
+// lane t of each group for LPE <= 16; for LPE = 32 both rows of a group hold
+// the same 16 entries, steps 0..15 in one register pair and 16..31 in a
+// second. (Loading them permuted instead touches four times the lines per
+// load.) The byte offset of an entry's B row is one multiply by the lane that
+// loaded it, and the descriptor's range check returns zeros for the entries
+// past the end of a run, so no step has a branch, a lane mask or 64-bit
+// address arithmetic: 6 vector instructions per 1 KB gather, against about 25
+// with a ds_bpermute broadcast per step, each of which the next gather waited
+// for.
+constexpr uint32_t kNoEntry = 0xFFFFF000u;  // offset past every operand the descriptor may cover
+constexpr uint64_t kBufMax = kNoEntry;      // operands read through a descriptor are smaller than this
+
+// lane T of the caller's entry-group (of its row of 16 for LPE = 32)
+template <int LPE, int T>
+__device__ __forceinline__ int32_t bcast(int32_t x) {
+    if constexpr (LPE >= 16) {
+        return __builtin_amdgcn_update_dpp(0, x, 0x150 + T, 0xf, 0xf, true);  // row_newbcast:T
+    } else if constexpr (LPE == 8) {  // two groups per row: lanes 0-7, then lanes 8-15
+        const int32_t lo = __builtin_amdgcn_update_dpp(0, x, 0x150 + T, 0xf, 0xf, true);
+        return __builtin_amdgcn_update_dpp(lo, x, 0x150 + 8 + T, 0xf, 0xc, false);
+    } else {
+        static_assert(LPE == 4, "lane layouts");
+        return __builtin_amdgcn_update_dpp(0, x, T * 0x55, 0xf, 0xf, true);  // quad_perm:[T,T,T,T]
+    }
+}
+
+struct Operand {
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t lane_off;  // byte offset of this lane's features within a row
+};
+
+// row: the byte offset of my entry's B row, kNoEntry if there is none
+template <int LPE, int T>
+__device__ __forceinline__ vf4 gather(const Operand &op, int32_t row) {
+    const uint32_t at = (uint32_t)bcast<LPE, T>(row) + op.lane_off;
+    return __builtin_bit_cast(vf4, __builtin_amdgcn_raw_buffer_load_b128(op.rsrc, at, 0, 0));
+}
+
+// The entries of one 64-entry run, as the lanes hold them: register pair q
+// has the entries of steps 16 q .. 16 q + 15.
+template <int LPE>
+struct Run {
+    static constexpr int kGroups = kWave / LPE;
+    static constexpr int kSteps = kWave / kGroups;           // steps of a whole run
+    static constexpr int kPairSteps = LPE < 16 ? LPE : 16;   // steps one register pair covers
+    static constexpr int kPairs = kSteps / kPairSteps;
+    static constexpr int kBlocks = kSteps / 4;               // steps are taken four at a time
+    int32_t row[kPairs];
+    float v[kPairs];
+};
+
+// Four steps' gathers, and their products.
+template <int LPE, int BLK, int... U>
+__device__ __forceinline__ void issue4(const Operand &op, const Run<LPE> &run, vf4 (&b)[4],
+                                       std::integer_sequence<int, U...>) {
+    constexpr int T0 = BLK * 4 % Run<LPE>::kPairSteps, q = BLK * 4 / Run<LPE>::kPairSteps;
+    ((b[U] = gather<LPE, T0 + U>(op, run.row[q])), ...);
+}
+template <int LPE, int BLK, int... U>
+__device__ __forceinline__ void add4(const Run<LPE> &run, const vf4 (&b)[4], float (&a)[4],
+                                     std::integer_sequence<int, U...>) {
+    constexpr int T0 = BLK * 4 % Run<LPE>::kPairSteps, q = BLK * 4 / Run<LPE>::kPairSteps;
+    const auto add = [&](float v, const vf4 &x) {
+        a[0] = fmaf(v, x.x, a[0]);
+        a[1] = fmaf(v, x.y, a[1]);
+        a[2] = fmaf(v, x.z, a[2]);
+        a[3] = fmaf(v, x.w, a[3]);
+    };
+    (add(__int_as_float(bcast<LPE, T0 + U>(__float_as_int(run.v[q]))), b[U]), ...);
+}
+
+// Blocks 0 .. NB - 1 of a run in straight-line code, four to eight gathers in
+// flight: block b + 2 is issued when block b has been added. `behind` (the
+// load of the next run's entries) goes behind the first gathers, so that no
+// gather waits for it.
+template <int LPE, int NB, int BLK = 0, typename F>
+__device__ __forceinline__ void run_blocks(const Operand &op, const Run<LPE> &run, vf4 (&b0)[4],
+                                           vf4 (&b1)[4], float (&a)[4], F behind) {
+    using four = std::make_integer_sequence<int, 4>;
+    if constexpr (BLK == 0) {
+        issue4<LPE, 0>(op, run, b0, four{});
+        if constexpr (NB > 1) issue4<LPE, 1>(op, run, b1, four{});
+        behind();
+        __builtin_amdgcn_sched_barrier(0);  // all of them before the first wait
+    }
+    add4<LPE, BLK>(run, b0, a, four{});
+    if constexpr (BLK + 2 < NB) issue4<LPE, BLK + 2>(op, run, b0, four{});
+    if constexpr (BLK + 1 < NB) run_blocks<LPE, NB, BLK + 1>(op, run, b1, b0, a, behind);
+}
+
+// The run's first nb blocks (1 <= nb <= kBlocks, wave-uniform).
+template <int LPE, int NB = 1>
+__device__ __forceinline__ void run_first(const Operand &op, const Run<LPE> &run, int32_t nb, float (&a)[4]) {
+    if (NB == Run<LPE>::kBlocks || nb == NB) {
+        vf4 b0[4], b1[4];
+        run_blocks<LPE, NB>(op, run, b0, b1, a, [] {});
+    } else if constexpr (NB < Run<LPE>::kBlocks) {
+        run_first<LPE, NB + 1>(op, run, nb, a);
+    }
+}
+
+// Sums the entries of runs beg, beg + stride, ... (< end; stride >= 64, beg <
+// end): each group's fp32 sum over its share of a run is folded into the
+// lane's fp64 acc. Every run but the last is whole.
+template <int LPE>
+__device__ __forceinline__ void accumulate_groups(const int32_t *__restrict__ col, const float *__restrict__ val,
+                                                  const Operand &op, uint32_t ldb_bytes, int64_t beg,
+                                                  int64_t end, int32_t stride, int lane, double (&acc)[4]) {
+    using R = Run<LPE>;
+    constexpr int kPairEntries = R::kPairSteps * R::kGroups;
+    // lane that loaded this lane's entry of a run (pair q's is kPairEntries further on)
+    const int32_t e0 = (lane % R::kPairSteps) * R::kGroups + lane / LPE;
+    int32_t nc;
+    float nv;
+    const auto load = [&](int64_t base) {  // past the end: the row's last entry, masked by take()
+        const int64_t p = min<int64_t>(base + lane, end - 1);
+        nc = __builtin_nontemporal_load(col + p);
+        nv = __builtin_nontemporal_load(val + p);
+    };
+    R run;
+    const auto take = [&](int64_t base, bool whole) {
+        const bool in = whole || base + lane < end;
+        const int32_t r = in ? (int32_t)((uint32_t)(nc & kColMask) * ldb_bytes) : (int32_t)kNoEntry;
+        const float v = in ? nv : 0.f;
+#pragma unroll
+        for (int q = 0; q < R::kPairs; ++q) {
+            run.row[q] = __shfl(r, e0 + q * kPairEntries);
+            run.v[q] = __shfl(v, e0 + q * kPairEntries);
+        }
+    };
+    const auto fold = [&](const float(&a)[4]) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x] += (double)a[x];
+    };
+    load(beg);
+    int64_t base = beg;  // int64: base + stride may pass 2^31 - 1
+    for (; base + stride < end; base += stride) {
+        take(base, true);
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        vf4 b0[4], b1[4];
+        run_blocks<LPE, R::kBlocks>(op, run, b0, b1, a, [&] { load(base + stride); });
+        fold(a);
+    }
+    take(base, false);
+    float a[4] = {0.f, 0.f, 0.f, 0.f};
+    const int32_t left = __builtin_amdgcn_readfirstlane((int32_t)min<int64_t>(kWave, end - base));
+    run_first<LPE>(op, run, (left + 4 * R::kGroups - 1) / (4 * R::kGroups), a);
+    fold(a);
+}
+
+// The same sums with 64-bit addresses and a lane mask per step; kHint as in
+// accumulate_runs.
+template <int LPE, bool kHint>
+__device__ __forceinline__ void accumulate_groups_wide(const int32_t *__restrict__ col,
+                                                       const float *__restrict__ val, const float *__restrict__ B,
+                                                       int64_t ldb, int64_t beg, int64_t end, int32_t stride,
+                                                       bool act, int lane, double (&acc)[4]) {
+    constexpr int G = kWave / LPE;
+    const int g = lane / LPE, sl = lane % LPE;
+    for (int64_t base = beg; base < end; base += stride) {
+        const int32_t cnt = __builtin_amdgcn_readfirstlane((int32_t)min<int64_t>(kWave, end - base));
+        int32_t my_c = 0;
+        float my_v = 0.f;
+        if (lane < cnt) {
+            my_c = __builtin_nontemporal_load(col + base + lane);
+            my_v = __builtin_nontemporal_load(val + base + lane);
+        }
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+                    constexpr int kSteps = kWave / G;  // steps that cover the 64-entry run
+                    constexpr int kWin = G >= 8 ? 4 : kUnroll;  // steps per window (gathers in flight)
+                    // one window of kUnroll steps at a time: unrolling the step loop
+                    // too keeps every window's (col, val) live at once (130 VGPRs for
+                    // G = 2) and costs occupancy
+        #pragma unroll 1
+                    for (int t0 = 0; t0 < kSteps; t0 += kWin) {
+                        if (t0 * G >= cnt) break;  // wave-uniform
+                        float4 b[kWin];
+                        float v[kWin];
+        #pragma unroll
+                        for (int u = 0; u < kWin; ++u) {
+                            const int j = (t0 + u) * G + g;  // entry of this group within the run
+                            const int32_t cf = __shfl(my_c, j & (kWave - 1));
+                            const int32_t c = cf & kColMask;
+                            const float vv = __shfl(my_v, j & (kWave - 1));
+                            b[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                            v[u] = 0.f;
+                            if (t0 + u < kSteps && j < cnt && act) {
+                                const float4 *brow = reinterpret_cast<const float4 *>(B + (int64_t)c * ldb) + sl;
+                                b[u] = (kHint && cf >= 0) ? load_nt(brow) : *brow;
+                                v[u] = vv;
+                            }
+                        }
+        #pragma unroll
+                        for (int u = 0; u < kWin; ++u) {
+                            a[0] = fmaf(v[u], b[u].x, a[0]);
+                            a[1] = fmaf(v[u], b[u].y, a[1]);
+                            a[2] = fmaf(v[u], b[u].z, a[2]);
+                            a[3] = fmaf(v[u], b[u].w, a[3]);
+                        }
+                    }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x] += (double)a[x];
+    }
+}
+
+// Adds the groups' sums; every lane of a group ends with the total of its
+// features. Fixed order.
+template <int LPE, typename T>
+__device__ __forceinline__ void sum_groups(T (&a)[4]) {
+#pragma unroll
+    for (int m = LPE; m < kWave; m <<= 1)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) a[x] += __shfl_xor(a[x], m);
+}
+
+// What a wave accumulates for one row with either kind of layout.
+template <int LPE, int NV, bool kHint, bool kBuf>
+__device__ __forceinline__ void accumulate(const int32_t *__restrict__ col, const float *__restrict__ val,
+                                           const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, int64_t beg,
+                                           int64_t end, int32_t stride, int32_t d, int lane, double (&acc)[NV][4]) {
+    if constexpr (LPE == kWave) {
+        bool act[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) act[q] = 4 * lane + 4 * kWave * q < d;
+        accumulate_runs<NV, kHint>(col, val, B, ldb, beg, end, stride, act, lane, acc);
+    } else {
+        static_assert(NV == 1, "the sliced layouts hold one float4 per lane");
+        if constexpr (kBuf) {
+            static_assert(!kHint, "the hint takes the wide form");
+            // a lane past the last feature reads the last one's vector again (no
+            // further line is touched); its sums are never stored
+            Operand op;
+            op.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(B), 0, b_bytes, 0x00027000);
+            op.lane_off = 16u * min(lane % LPE, (d - 1) / 4);
+            if (beg < end) accumulate_groups<LPE>(col, val, op, (uint32_t)(4 * ldb), beg, end, stride, lane, acc[0]);
+        } else {
+            accumulate_groups_wide<LPE, kHint>(col, val, B, ldb, beg, end, stride, 4 * (lane % LPE) < d, lane,
+                                               acc[0]);
+        }
     }
 }
 
@@ -249,20 +461,16 @@ __device__ __forceinline__ void store_row(float *__restrict__ yrow, int32_t d, i
 // 64 entries and their fp64 sums are added in LDS in fixed wave order.
 // Row r spans [ptr[r], ptr[r + off]) and is written to row r of Y.
 // B and Y point at the first feature of the current slice; d is its width.
-template <int LPE, int NV, bool kHint>
+template <int LPE, int NV, bool kHint, bool kBuf>
 __global__ __launch_bounds__(kSpmmLongWaves * 64) void spmm_long_kernel(
     const int32_t *__restrict__ ptr, int64_t off, const int32_t *__restrict__ col, const float *__restrict__ val,
-    const float *__restrict__ B, int64_t ldb, float *__restrict__ Y, int64_t ldy, int32_t d,
+    const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, float *__restrict__ Y, int64_t ldy, int32_t d,
     const int32_t *__restrict__ long_count, int32_t *__restrict__ long_next,
     const int32_t *__restrict__ long_rows) {
     __shared__ double red[kSpmmLongWaves][NV * 4][kWave];
     __shared__ int32_t s_job;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int sl = lane % LPE;
-    bool act[NV];
-#pragma unroll
-    for (int q = 0; q < NV; ++q) act[q] = 4 * sl + 4 * kWave * q < d;
     const int32_t nl = __builtin_amdgcn_readfirstlane(*long_count);
     for (;;) {
         if (threadIdx.x == 0) s_job = atomicAdd(long_next, 1);
@@ -275,8 +483,8 @@ __global__ __launch_bounds__(kSpmmLongWaves * 64) void spmm_long_kernel(
         double acc[NV][4];
 #pragma unroll
         for (int q = 0; q < NV; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
-        accumulate_runs<LPE, NV, kHint>(col, val, B, ldb, (int64_t)s + kWave * wave, e, kWave * kSpmmLongWaves, act,
-                                 lane, acc);
+        accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, (int64_t)s + kWave * wave, e,
+                                         kWave * kSpmmLongWaves, d, lane, acc);
 #pragma unroll
         for (int q = 0; q < NV; ++q)
 #pragma unroll
@@ -291,6 +499,7 @@ __global__ __launch_bounds__(kSpmmLongWaves * 64) void spmm_long_kernel(
                     for (int w = 1; w < kSpmmLongWaves; ++w) t += red[w][q * 4 + x][lane];
                     acc[q][x] = t;
                 }
+            if constexpr (LPE < kWave) sum_groups<LPE>(acc[0]);
             store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
         }
         __syncthreads();  // red and s_job are reused by the next row
@@ -303,17 +512,13 @@ __global__ __launch_bounds__(kSpmmLongWaves * 64) void spmm_long_kernel(
 // long rows): a processing order only, each row's sum is unchanged. Row r
 // spans [ptr[r], ptr[r + off]); kCsr says off == 1 (a CSR row pointer, both
 // bounds then come from one 8-byte scalar load).
-template <int LPE, int NV, bool kCsr, bool kHint>
+template <int LPE, int NV, bool kCsr, bool kHint, bool kBuf>
 __global__ __launch_bounds__(kSpmmRowWaves * 64) void spmm_rows_kernel(
     const int32_t *__restrict__ ptr, int64_t off, const int32_t *__restrict__ col, const float *__restrict__ val,
-    const float *__restrict__ B, int64_t ldb, float *__restrict__ Y, int64_t ldy, int32_t n_rows,
+    const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, float *__restrict__ Y, int64_t ldy, int32_t n_rows,
     int32_t d, int32_t skip_long, const int32_t *__restrict__ order, const int32_t *__restrict__ long_count) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int sl = lane % LPE;
-    bool act[NV];
-#pragma unroll
-    for (int q = 0; q < NV; ++q) act[q] = 4 * sl + 4 * kWave * q < d;
     int32_t r = blockIdx.x * kSpmmRowWaves + wave;
     if (order) {
         const int64_t i = (int64_t)__builtin_amdgcn_readfirstlane(*long_count) + r;
@@ -328,8 +533,27 @@ __global__ __launch_bounds__(kSpmmRowWaves * 64) void spmm_rows_kernel(
     double acc[NV][4];
 #pragma unroll
     for (int q = 0; q < NV; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
-    accumulate_runs<LPE, NV, kHint>(col, val, B, ldb, s, e, kWave, act, lane, acc);
+    accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, s, e, kWave, d, lane, acc);
+    if constexpr (LPE < kWave) {
+        if (e - s <= kWave) {  // one run: acc holds fp32 sums, which are added in fp32
+            float a[4] = {(float)acc[0][0], (float)acc[0][1], (float)acc[0][2], (float)acc[0][3]};
+            sum_groups<LPE>(a);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) acc[0][x] = a[x];
+        } else {
+            sum_groups<LPE>(acc[0]);
+        }
+    }
     store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
+}
+
+// Bytes of B that a pass over dl features may read, counted from the first
+// one (whole 16-byte vectors, ld % 4 == 0); 0 when they pass what
+// a buffer descriptor's 32-bit offsets cover below kNoEntry.
+inline uint32_t buffer_bytes(int32_t n_cols, int64_t ldb, int32_t dl) {
+    if (n_cols <= 0) return 0;
+    const __int128 bytes = 4 * ((__int128)(n_cols - 1) * ldb + (dl + 3) / 4 * 4);
+    return bytes < (__int128)kBufMax ? (uint32_t)bytes : 0u;
 }
 
 constexpr int kClasses = 32;
@@ -449,7 +673,9 @@ inline bool use_order(int32_t n_rows, int64_t nnz) {
 // of row r in fixed order b = 0..P-1 in fp64 and rounds once.
 constexpr int kBlockW = 64;                         // features per blocked pass, the widest layout
 constexpr double kBlockBytes = 4.5 * 1024 * 1024;   // B bytes per column range (~ one XCD's L2)
-constexpr int kMaxBlocks = 8;                       // partial outputs at most 8 x Y per pass
+constexpr double kFineBytes = 3.0 * 1024 * 1024;    // and for 64-float passes when the pieces stay long
+constexpr int kMaxBlocks = 12;                      // partial outputs at most 12 x Y per pass
+constexpr int kCoarseBlocks = 8;                    // ... 8 x with ranges of kBlockBytes
 constexpr int kPieceMin = 56;                       // mean entries per piece of a row for blocking
 
 // Features per blocked pass for feature width d: the narrowest of the 16-,
@@ -471,19 +697,30 @@ inline int32_t blocked_width(int32_t d) { return d <= 16 ? 16 : d <= 32 ? 32 : k
 // 489 entries per row, 8 ranges of 7.5 MB measured 5 % faster than
 // unblocked passes at d = 256, while 32-float passes over ranges that do
 // fit L2 were slower: twice the passes over the row structure).
+// 64-float passes over long rows take ranges of 3 MiB instead, up to 12 of
+// them while a piece keeps kPieceMin entries: a range of 4.24 MB does not
+// quite fit an L2 that col, val and the partial rows stream through as well
+// (132,534 nodes, 600 entries per row, d = 256: 14 % of the gathers missed;
+// 4.68 ms with 8 ranges, 4.53 with 10, 4.49 with 12 of 50 entries each, 4.73
+// with 16). The narrower layouts and shorter rows lose by it (30 % of that
+// graph's columns: 1.53 ms with 3 ranges, 1.61 with 4).
 // RSC_SPMM_BLOCKED=0 switches the mode off, =2..8 forces that P.
-inline int32_t column_blocks(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d) {
+inline int32_t column_blocks(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d, bool fine = true) {
     if (n_rows <= 0 || (int64_t)(kMaxBlocks + 1) * n_rows > INT32_MAX) return 1;  // virtual rows are int32
     if (const char *env = getenv("RSC_SPMM_BLOCKED")) {
         const int v = atoi(env);
         if (v == 0) return 1;
-        if (v >= 2 && v <= kMaxBlocks) return v;
+        if (v >= 2 && v <= kCoarseBlocks) return v;
     }
     const int32_t W = blocked_width(d);
     int64_t P = (int64_t)std::ceil((double)n_src * W * 4 / kBlockBytes);
-    if (P < 2 || P > 2 * kMaxBlocks) return 1;
-    P = std::min<int64_t>(P, kMaxBlocks);
+    if (P < 2 || P > 2 * kCoarseBlocks) return 1;
+    P = std::min<int64_t>(P, kCoarseBlocks);
     if (nnz < (int64_t)kPieceMin * (kBlockW / W) * P * n_rows) return 1;
+    if (fine && W == kBlockW) {
+        const int64_t r = (int64_t)std::ceil((double)n_src * W * 4 / kFineBytes);
+        P = std::max(P, std::min<int64_t>({r, kMaxBlocks, nnz / ((int64_t)kPieceMin * n_rows)}));
+    }
     return (int32_t)P;
 }
 
@@ -673,8 +910,10 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     // The blocked mode is chosen from the expected entries and referenced B
     // rows (the same for the exact product and a full-budget slice of it);
     // it runs only when the workspace holds its buffers.
-    const int32_t P = column_blocks(n_rows, nnz_hint, n_src_hint, d);
+    int32_t P = column_blocks(n_rows, nnz_hint, n_src_hint, d);
     const size_t head = sizeof(SpmmWs) + list_bytes(n_rows, nnz_bound);
+    if (P > 1 && head + blocked_bytes(n_rows, P) > ws_bytes)  // a fixed scratch may hold the coarser ranges
+        P = column_blocks(n_rows, nnz_hint, n_src_hint, d, false);
     if (P > 1 && head + blocked_bytes(n_rows, P) <= ws_bytes) {
         // the long-piece list must hold every piece the collect pass can find
         if (P > kMaxBlocks || long_pieces_bound(n_rows, nnz_bound, P) > list_entries(n_rows, nnz_bound))
@@ -709,15 +948,24 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
         const int32_t W = blocked_width(d);
         for (int32_t f0 = 0; f0 < d; f0 += W) {
             const int32_t dl = std::min<int32_t>(d - f0, W);
-#define RSC_SPMM_BLOCKED_LAUNCH(LPE_)                                                                         \
+            const uint32_t bb = buffer_bytes(n_cols, ldb, dl);
+#define RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, BUF_)                                                                 \
     do {                                                                                                      \
         if (n_long > 0) {                                                                                     \
             if (f0 > 0 || pre) zero_next_kernel<<<1, 1, 0, stream>>>(&h->long_next);                          \
-            spmm_long_kernel<LPE_, 1, false><<<n_long, kSpmmLongWaves * 64, 0, stream>>>(                     \
-                S, n_rows, col, val, B + f0, ldb, part, W, dl, &h->long_count, &h->long_next, list);          \
+            spmm_long_kernel<LPE_, 1, false, BUF_><<<n_long, kSpmmLongWaves * 64, 0, stream>>>(               \
+                S, n_rows, col, val, B + f0, ldb, bb, part, W, dl, &h->long_count, &h->long_next, list);      \
         }                                                                                                     \
-        spmm_rows_kernel<LPE_, 1, false, false><<<vgrid, kSpmmRowWaves * 64, 0, stream>>>(                    \
-            S, n_rows, col, val, B + f0, ldb, part, W, nv, dl, n_long > 0 ? 1 : 0, nullptr, &h->long_count);  \
+        spmm_rows_kernel<LPE_, 1, false, false, BUF_><<<vgrid, kSpmmRowWaves * 64, 0, stream>>>(              \
+            S, n_rows, col, val, B + f0, ldb, bb, part, W, nv, dl, n_long > 0 ? 1 : 0, nullptr,               \
+            &h->long_count);                                                                                  \
+    } while (0)
+#define RSC_SPMM_BLOCKED_LAUNCH(LPE_)                  \
+    do {                                               \
+        if (bb != 0)                                   \
+            RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, true);     \
+        else                                           \
+            RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, false);    \
     } while (0)
             if (W == 16)
                 RSC_SPMM_BLOCKED_LAUNCH(4);
@@ -725,6 +973,7 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
                 RSC_SPMM_BLOCKED_LAUNCH(8);
             else
                 RSC_SPMM_BLOCKED_LAUNCH(16);
+#undef RSC_SPMM_BLOCKED_LAUNCH_B
 #undef RSC_SPMM_BLOCKED_LAUNCH
             const int64_t nc = (int64_t)n_rows * ((dl + 3) / 4);
             combine_blocks_kernel<<<(unsigned)ceil_div(nc, 256), 256, 0, stream>>>(part, W, n_rows, P, dl,
@@ -754,33 +1003,45 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     const bool hint = hint_cols && spmm_hint_taken(n_src_hint, d, slice);
     for (int32_t f0 = 0; f0 < d;) {
         const int32_t dl = std::min<int32_t>(d - f0, slice);
-#define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_)                                                               \
+        const uint32_t bb = buffer_bytes(n_cols, ldb, dl);
+#define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_, BUF_)                                                         \
     do {                                                                                               \
         if (n_long_blocks > 0) {                                                                       \
             if (f0 > 0 || pre) zero_next_kernel<<<1, 1, 0, stream>>>(&h->long_next);                   \
-            spmm_long_kernel<LPE_, NV_, H_><<<n_long_blocks, kSpmmLongWaves * 64, 0, stream>>>(         \
-                rowptr, 1, col, val, B + f0, ldb, Y + f0, ldy, dl, &h->long_count, &h->long_next, list);  \
+            spmm_long_kernel<LPE_, NV_, H_, BUF_><<<n_long_blocks, kSpmmLongWaves * 64, 0, stream>>>(   \
+                rowptr, 1, col, val, B + f0, ldb, bb, Y + f0, ldy, dl, &h->long_count, &h->long_next,  \
+                list);                                                                                 \
         }                                                                                              \
-        spmm_rows_kernel<LPE_, NV_, true, H_><<<grid, kSpmmRowWaves * 64, 0, stream>>>(                \
-            rowptr, 1, col, val, B + f0, ldb, Y + f0, ldy, n_rows, dl, n_long_blocks > 0 ? 1 : 0, order,  \
-            &h->long_count);                                                                           \
+        spmm_rows_kernel<LPE_, NV_, true, H_, BUF_><<<grid, kSpmmRowWaves * 64, 0, stream>>>(          \
+            rowptr, 1, col, val, B + f0, ldb, bb, Y + f0, ldy, n_rows, dl, n_long_blocks > 0 ? 1 : 0,  \
+            order, &h->long_count);                                                                    \
     } while (0)
-#define RSC_SPMM_LAUNCH(LPE_, NV_)                   \
-    do {                                             \
-        if (hint)                                    \
-            RSC_SPMM_LAUNCH_H(LPE_, NV_, true);      \
-        else                                         \
-            RSC_SPMM_LAUNCH_H(LPE_, NV_, false);     \
+#define RSC_SPMM_LAUNCH_SLICED(LPE_)                     \
+    do {                                                 \
+        if (hint)                                        \
+            RSC_SPMM_LAUNCH_H(LPE_, 1, true, false);     \
+        else if (bb != 0)                                \
+            RSC_SPMM_LAUNCH_H(LPE_, 1, false, true);     \
+        else                                             \
+            RSC_SPMM_LAUNCH_H(LPE_, 1, false, false);    \
+    } while (0)
+#define RSC_SPMM_LAUNCH(NV_)                             \
+    do {                                                 \
+        if (hint)                                        \
+            RSC_SPMM_LAUNCH_H(64, NV_, true, false);     \
+        else                                             \
+            RSC_SPMM_LAUNCH_H(64, NV_, false, false);    \
     } while (0)
         switch (slice) {
-            case 16: RSC_SPMM_LAUNCH(4, 1); break;
-            case 32: RSC_SPMM_LAUNCH(8, 1); break;
-            case 64: RSC_SPMM_LAUNCH(16, 1); break;
-            case 128: RSC_SPMM_LAUNCH(32, 1); break;
+            case 16: RSC_SPMM_LAUNCH_SLICED(4); break;
+            case 32: RSC_SPMM_LAUNCH_SLICED(8); break;
+            case 64: RSC_SPMM_LAUNCH_SLICED(16); break;
+            case 128: RSC_SPMM_LAUNCH_SLICED(32); break;
             default:
-                if (dl <= 4 * kWave) RSC_SPMM_LAUNCH(64, 1); else RSC_SPMM_LAUNCH(64, 2);
+                if (dl <= 4 * kWave) RSC_SPMM_LAUNCH(1); else RSC_SPMM_LAUNCH(2);
         }
 #undef RSC_SPMM_LAUNCH
+#undef RSC_SPMM_LAUNCH_SLICED
 #undef RSC_SPMM_LAUNCH_H
         f0 += dl;
     }
