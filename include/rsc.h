@@ -128,8 +128,8 @@ rsc_status_t rsc_spmm(const rsc_csr_t *A, const float *B, int32_t d, int64_t ldb
  * graph capture, tight serving loops, harnesses that forbid allocation): the
  * same product with no workspace argument and no allocation. Its scratch is
  * a static 32 MiB device array inside the library, one per GPU, held until
- * the process ends; a product needs 512 bytes plus 4 max(n_rows,
- * min(12 n_rows, nnz / 1025)) bytes of it (about 8.3M rows at most), beyond
+ * the process ends; a product needs 512 bytes plus 4 n_rows bytes of it
+ * (about 8.3M rows at most), beyond
  * which the call returns RSC_ERR_CAPACITY without launching. A product whose
  * column-blocked buffers do not also fit runs unblocked (then Y may differ
  * from rsc_spmm's within rounding; otherwise it is bitwise equal). Every
@@ -167,7 +167,7 @@ rsc_status_t rsc_spmm_noalloc(const rsc_csr_t *A, const float *B, int32_t d, int
  * bytes for the split bounds and the workspace (stream-ordered, on `stream`);
  * RSC_ERR_OUT_OF_MEMORY if that fails. Runs of one plan share its workspace, so they must be
  * ordered on the device. The sampled-matrix cache prepares each new slice's
- * row list the same way at refresh time; its sampled products do not take
+ * row order or split bounds at refresh time; its sampled products do not take
  * the column hint (on the cached slices it measured slower). */
 typedef struct rsc_spmm_plan rsc_spmm_plan_t;
 rsc_status_t rsc_spmm_plan_create(const rsc_csr_t *A, hipStream_t stream, rsc_spmm_plan_t **out);

@@ -403,8 +403,8 @@ rsc_status_t rsc_spmm_plan_create(const rsc_csr_t *A, hipStream_t stream, rsc_sp
         plan_free(p, stream);
         return fail(RSC_ERR_OUT_OF_MEMORY, "plan workspace of %zu bytes", p->ws_bytes);
     }
-    // the per-call preparation of the product, done once: split bounds and
-    // long-piece list (column-blocked), or the long-row list / row order
+    // the per-call preparation of the product, done once: split bounds
+    // (column-blocked), or the long-row list / row order
     // (prepared for feature widths of 33 and more; a narrower product whose
     // range count differs prepares for itself on every run)
     const int32_t P = std::max(1, rsc::spmm_column_blocks(A->n_rows, A->nnz, A->n_cols, 64));
@@ -413,13 +413,14 @@ rsc_status_t rsc_spmm_plan_create(const rsc_csr_t *A, hipStream_t stream, rsc_sp
         if (P > 1) {
             e = hipMallocAsync((void **)&p->split, sizeof(int32_t) * (size_t)A->n_rows * (P + 1), stream);
             if (e == hipSuccess) e = rsc::spmm_split_launch(A->n_rows, A->n_cols, A->rowptr, A->col, P, p->split, stream);
-            if (e == hipSuccess) e = rsc::spmm_blocked_prepare(A->n_rows, A->nnz, p->split, P, p->ws, stream);
         } else {
             p->prep.ordered = rsc::spmm_use_order(A->n_rows, A->nnz);
-            e = rsc::spmm_rows_prepare(A->n_rows, A->nnz, A->rowptr, p->ws, stream);
         }
+        // (also when blocked: without long rows there are no long pieces)
+        if (e == hipSuccess) e = rsc::spmm_rows_prepare(A->n_rows, A->nnz, A->rowptr, p->ws, stream);
         int32_t long_rows = 0;
-        const bool has_list = P > 1 || p->prep.ordered || std::min<int64_t>(A->n_rows, A->nnz / 1025) > 0;
+        const bool has_list =
+            rsc::spmm_use_order(A->n_rows, A->nnz) || std::min<int64_t>(A->n_rows, A->nnz / 1025) > 0;
         if (e == hipSuccess && has_list && A->n_rows > 0)
             e = hipMemcpyAsync(&long_rows, rsc::spmm_long_count_of(p->ws), sizeof long_rows, hipMemcpyDeviceToHost,
                                stream);
@@ -433,6 +434,7 @@ rsc_status_t rsc_spmm_plan_create(const rsc_csr_t *A, hipStream_t stream, rsc_sp
         p->prep.split = p->split;
         p->prep.P = P;
         p->prep.long_rows = long_rows;
+        p->prep.list = P == 1;
         p->prep.ready = true;
     }
     if (hint_worthwhile(A->n_cols) && A->nnz > 0) {
@@ -517,7 +519,7 @@ rsc_status_t rsc_spmm_noalloc(const rsc_csr_t *A, const float *B, int32_t d, int
     RSC_TRY(check_csr(A, "A"));
     RSC_TRY(check_dense(B, A->n_cols, d, ldb, "B"));
     RSC_TRY(check_dense(Y, A->n_rows, d, ldy, "Y"));
-    const size_t need = rsc::spmm_core_ws_bytes(A->n_rows, A->nnz);
+    const size_t need = rsc::spmm_core_ws_bytes(A->n_rows);
     if (need > kNoallocScratchBytes)
         return fail(RSC_ERR_CAPACITY,
                     "rsc_spmm_noalloc: %d rows and %lld entries need %zu bytes of scratch; the static scratch "
@@ -784,10 +786,9 @@ static rsc_status_t keep_previous_selection(rsc_cache_t *c, hipStream_t stream) 
 }
 
 // After a new slice: what every sampled product of feature width d (the
-// last scored operand's) would build first (split bounds and long-piece list
-// when blocked, else the long-row list or the row order), built once into
-// ws_spmm. Asynchronous (the list's length stays on the device; launches use
-// its bound).
+// last scored operand's) would build first (split bounds when blocked, else
+// the row order where it is used), built once. Asynchronous (the number of
+// long rows stays on the device).
 static hipError_t cache_prepare(rsc_cache_t *c, int32_t d, hipStream_t stream) {
     c->prep = rsc::SpmmPrepared{};
     const rsc_csr_t &X = c->X;
@@ -797,13 +798,13 @@ static hipError_t cache_prepare(rsc_cache_t *c, int32_t d, hipStream_t stream) {
     const int32_t P = std::max(1, rsc::spmm_column_blocks(X.n_rows, nnz_hint, kk, d));
     hipError_t e;
     if (P > 1) {
-        if (P > c->split_P || rsc::spmm_blocked_fits(X.n_rows, X.nnz, P) > c->ws_spmm_bytes) return hipSuccess;
+        if (P > c->split_P || rsc::spmm_blocked_fits(X.n_rows, P) > c->ws_spmm_bytes) return hipSuccess;
         e = rsc::spmm_split_launch(X.n_rows, X.n_cols, c->s_rowptr, c->s_col, P, c->s_split, stream);
-        if (e == hipSuccess) e = rsc::spmm_blocked_prepare(X.n_rows, X.nnz, c->s_split, P, c->ws_spmm, stream);
         c->prep.split = c->s_split;
     } else {
         c->prep.ordered = rsc::spmm_use_order(X.n_rows, X.nnz);
-        e = rsc::spmm_rows_prepare(X.n_rows, X.nnz, c->s_rowptr, c->ws_spmm, stream);
+        c->prep.list = c->prep.ordered || (c->x_long_rows != 0 && rsc::spmm_lists_long_rows(X.n_rows));
+        e = c->prep.list ? rsc::spmm_rows_prepare(X.n_rows, X.nnz, c->s_rowptr, c->ws_spmm, stream) : hipSuccess;
     }
     c->prep.P = P;
     c->prep.long_rows = c->x_long_rows == 0 ? 0 : -1;  // else the length stays on the device

@@ -21,15 +21,17 @@ size_t spmm_ws_bytes(int32_t n_rows, int64_t nnz, int32_t n_cols);
 int32_t spmm_slice_width(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d);
 // What an SpMM plan prepared once for its operand: the column-blocked split
 // bounds (split, P; P = 1 for an unblocked product) and, in the plan's own
-// workspace, the long-row (or long-piece) list or the length-class order,
-// with long_rows their count (-1: not known on the host, the launch uses the
-// bound) and ordered the row-order decision taken.
+// workspace, the long-row list or the length-class order,
+// with long_rows their count (-1: not known on the host) and ordered the
+// row-order decision taken; list says that the workspace holds the list (or
+// the order), without it long rows are taken by the blocks that hold them.
 // A launch uses them only while its own decisions match (ready); one that
 // did not (*used_prep false) rebuilt the list in that workspace.
 struct SpmmPrepared {
     const int32_t *split = nullptr;
     int32_t P = 1;
     bool ordered = false;
+    bool list = false;
     bool ready = false;
     int32_t long_rows = 0;
 };
@@ -46,17 +48,16 @@ int32_t spmm_column_blocks(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d
 hipError_t spmm_split_launch(int32_t n_rows, int32_t n_cols, const int32_t *rowptr, const int32_t *col, int32_t P,
                              int32_t *S, hipStream_t stream);
 bool spmm_use_order(int32_t n_rows, int64_t nnz);
+bool spmm_lists_long_rows(int32_t n_rows);  // without a plan (unordered)
 // whether a pass `slice` floats wide over n_src B rows takes the hub hint
 // (on a column copy that carries it)
 bool spmm_hint_taken(int64_t n_src, int32_t d, int32_t slice);
 hipError_t spmm_rows_prepare(int32_t n_rows, int64_t nnz_bound, const int32_t *rowptr, void *ws,
                              hipStream_t stream);
-hipError_t spmm_blocked_prepare(int32_t n_rows, int64_t nnz_bound, const int32_t *S, int32_t P, void *ws,
-                                hipStream_t stream);
-size_t spmm_blocked_fits(int32_t n_rows, int64_t nnz_bound, int32_t P);  // workspace bytes the blocked mode needs
+size_t spmm_blocked_fits(int32_t n_rows, int32_t P);  // workspace bytes the blocked mode needs
 // workspace bytes an unblocked product needs (header and row list); with at
 // least this much a launch runs, blocked only if the blocked buffers also fit
-size_t spmm_core_ws_bytes(int32_t n_rows, int64_t nnz_bound);
+size_t spmm_core_ws_bytes(int32_t n_rows);
 const int32_t *spmm_long_count_of(const void *ws);
 
 // ---- gather-ceiling probe (measurement helper) ---------------------------

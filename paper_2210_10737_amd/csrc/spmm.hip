@@ -10,14 +10,13 @@
 //     coalesced, non-temporal load and broadcast from the owning lane with
 //     v_readlane into scalar registers, so each gathered B row is addressed
 //     by a scalar base plus the lane offset;
-//   * 8 gather instructions (4 in the layouts that take 8 or 16 entries per
-//     instruction) are issued before their FMAs for memory-level parallelism;
+//   * 4 to 8 gather instructions are in flight per wave;
 //   * products are accumulated in fp32 over each run of <= 64 entries and the
 //     run sum is folded into an fp64 accumulator; one fp32 rounding per output;
-//   * rows with more than kLongRow entries are taken by persistent 8-wave
-//     blocks: the waves take interleaved runs of 64 entries and their fp64
-//     sums are combined in LDS in fixed wave order. No float atomics, so the
-//     result is bitwise reproducible;
+//   * rows with more than kLongRow entries are taken by a whole block: the
+//     waves take interleaved runs of 64 entries and their fp64 sums are
+//     combined in LDS in fixed wave order. No float atomics, so the result is
+//     bitwise reproducible;
 //   * features up to 128 wide take a layout of 16..128 floats (several
 //     entries per load instruction), and B may be processed in several such
 //     feature slices when the slice of the referenced B rows gets close to
@@ -39,14 +38,20 @@
 
 namespace rsc {
 
-// Rows with more than kLongRow entries are processed by a whole 8-wave
-// block (waves take interleaved runs of 64 entries, then a fixed-order LDS
-// reduction); shorter rows by one wave. Long rows are handed out to
-// persistent blocks through an atomic counter.
+// Rows with more than kLongRow entries are processed by a whole block (its
+// waves take interleaved runs of 64 entries, then a fixed-order LDS
+// reduction); shorter rows by one wave.
 constexpr int kLongRow = 1024;
-constexpr int kSpmmRowWaves = 4;      // rows (waves) per block of the row kernel
-constexpr int kSpmmLongWaves = 8;     // waves per block of the long-row kernel
-constexpr int kSpmmLongBlocks = 1024;  // persistent blocks that walk the long-row list
+constexpr int kSpmmWaves = 4;          // waves per block, and short rows
+// Passes of 129 to 256 features (one entry per load) over rows of 32 entries
+// and more take 8 waves per block from this many rows on: 2,449,029 rows, mean
+// 51, d = 256: 16.48 ms against 16.60 with 4. On shorter rows (that graph's 30 %
+// slice, 5 per row) 4 waves are 1.4 % faster; fewer rows would leave compute
+// units without a block, and at 512 features 8 waves cost 13 %.
+constexpr int32_t kWideBlockRows = 16384;
+constexpr int32_t kWideBlockMean = 32;
+constexpr int kSpmmLongBlocks = 1024;  // blocks that walk a long-row list of unknown length
+constexpr int kSpmmLongBlocksMax = 8192;  // blocks for a list of known length (one row each up to here)
 
 namespace {
 
@@ -59,11 +64,9 @@ __device__ __forceinline__ float4 load_nt(const float4 *p) {
     return make_float4(x.x, x.y, x.z, x.w);
 }
 
-__global__ void zero_counters_kernel(int32_t *p) { p[0] = 0; p[1] = 0; }
-__global__ void zero_next_kernel(int32_t *p) { *p = 0; }
+__global__ void zero_count_kernel(int32_t *p) { *p = 0; }
 
-// Appends every row longer than kLongRow to `list`; row r spans
-// [ptr[r], ptr[r + end_off]) (end_off = 1 for a CSR row pointer). Each thread checks
+// Appends every row longer than kLongRow to `list`. Each thread checks
 // kCollectPerThread rows (coalesced reads); a block-wide scan gives each long
 // row its place, and one atomic per block reserves the block's range, so the
 // list costs a few hundred atomics rather than one per row. The list order
@@ -72,7 +75,7 @@ constexpr int kCollectThreads = 1024;
 constexpr int kCollectPerThread = 4;
 
 __global__ __launch_bounds__(kCollectThreads) void collect_long_rows_kernel(
-    const int32_t *__restrict__ ptr, int64_t end_off, int32_t n_rows, int32_t *count, int32_t *list) {
+    const int32_t *__restrict__ rowptr, int32_t n_rows, int32_t *count, int32_t *list) {
     __shared__ int32_t s_wave[kCollectThreads / 64];
     __shared__ int32_t s_base;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -82,7 +85,7 @@ __global__ __launch_bounds__(kCollectThreads) void collect_long_rows_kernel(
 #pragma unroll
     for (int i = 0; i < kCollectPerThread; ++i) {
         const int64_t r = base + t + (int64_t)kCollectThreads * i;
-        is_long[i] = r < n_rows && ptr[r + end_off] - ptr[r] > kLongRow;
+        is_long[i] = r < n_rows && rowptr[r + 1] - rowptr[r] > kLongRow;
         mine += is_long[i];
     }
     // exclusive scan of `mine` over the block: within the wave, then across waves
@@ -456,95 +459,129 @@ __device__ __forceinline__ void store_row(float *__restrict__ yrow, int32_t d, i
     }
 }
 
-// Long rows: persistent blocks of kSpmmLongWaves waves take rows from the list
-// through an atomic counter; within a row the waves take interleaved runs of
-// 64 entries and their fp64 sums are added in LDS in fixed wave order.
-// Row r spans [ptr[r], ptr[r + off]) and is written to row r of Y.
-// B and Y point at the first feature of the current slice; d is its width.
-template <int LPE, int NV, bool kHint, bool kBuf>
-__global__ __launch_bounds__(kSpmmLongWaves * 64) void spmm_long_kernel(
-    const int32_t *__restrict__ ptr, int64_t off, const int32_t *__restrict__ col, const float *__restrict__ val,
-    const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, float *__restrict__ Y, int64_t ldy, int32_t d,
-    const int32_t *__restrict__ long_count, int32_t *__restrict__ long_next,
-    const int32_t *__restrict__ long_rows) {
-    __shared__ double red[kSpmmLongWaves][NV * 4][kWave];
-    __shared__ int32_t s_job;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int32_t nl = __builtin_amdgcn_readfirstlane(*long_count);
-    for (;;) {
-        if (threadIdx.x == 0) s_job = atomicAdd(long_next, 1);
-        __syncthreads();
-        const int32_t j = __builtin_amdgcn_readfirstlane(s_job);
-        if (j >= nl) break;  // block-uniform: every wave read the same s_job
-        const int32_t r = __builtin_amdgcn_readfirstlane(long_rows[j]);
-        const int32_t s = __builtin_amdgcn_readfirstlane(ptr[r]);
-        const int32_t e = __builtin_amdgcn_readfirstlane(ptr[r + off]);
-        double acc[NV][4];
-#pragma unroll
-        for (int q = 0; q < NV; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
-        accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, (int64_t)s + kWave * wave, e,
-                                         kWave * kSpmmLongWaves, d, lane, acc);
-#pragma unroll
-        for (int q = 0; q < NV; ++q)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) red[wave][q * 4 + x][lane] = acc[q][x];
-        __syncthreads();
-        if (wave == 0) {
-#pragma unroll
-            for (int q = 0; q < NV; ++q)
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    double t = red[0][q * 4 + x][lane];
-                    for (int w = 1; w < kSpmmLongWaves; ++w) t += red[w][q * 4 + x][lane];
-                    acc[q][x] = t;
-                }
-            if constexpr (LPE < kWave) sum_groups<LPE>(acc[0]);
-            store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
-        }
-        __syncthreads();  // red and s_job are reused by the next row
-    }
-}
-
-// Short rows: one wave per row, kSpmmRowWaves rows per block; rows longer
-// than kLongRow are left to spmm_long_kernel when skip_long. With `order`,
-// the rows are taken in that order after its first *long_count entries (the
-// long rows): a processing order only, each row's sum is unchanged. Row r
-// spans [ptr[r], ptr[r + off]); kCsr says off == 1 (a CSR row pointer, both
-// bounds then come from one 8-byte scalar load).
-template <int LPE, int NV, bool kCsr, bool kHint, bool kBuf>
-__global__ __launch_bounds__(kSpmmRowWaves * 64) void spmm_rows_kernel(
-    const int32_t *__restrict__ ptr, int64_t off, const int32_t *__restrict__ col, const float *__restrict__ val,
-    const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, float *__restrict__ Y, int64_t ldy, int32_t n_rows,
-    int32_t d, int32_t skip_long, const int32_t *__restrict__ order, const int32_t *__restrict__ long_count) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    int32_t r = blockIdx.x * kSpmmRowWaves + wave;
-    if (order) {
-        const int64_t i = (int64_t)__builtin_amdgcn_readfirstlane(*long_count) + r;
-        if (i >= n_rows) return;
-        r = __builtin_amdgcn_readfirstlane(order[i]);
-    } else if (r >= n_rows) {
-        return;
-    }
-    const int32_t s = __builtin_amdgcn_readfirstlane(ptr[r]);
-    const int32_t e = __builtin_amdgcn_readfirstlane(kCsr ? ptr[r + 1] : ptr[(int64_t)r + off]);
-    if (skip_long && e - s > kLongRow) return;
+// A long row by the whole block: the waves' sums are added in wave order
+// through LDS and the last wave stores the total. Reached by every wave.
+template <int LPE, int NV, bool kHint, bool kBuf, int kWaves>
+__device__ __forceinline__ void take_long_row(const int32_t *__restrict__ col, const float *__restrict__ val,
+                                              const float *__restrict__ B, int64_t ldb, uint32_t b_bytes,
+                                              float *__restrict__ yrow, int32_t d, int32_t s, int32_t e, int lane,
+                                              int wave, double (*red)[kWave]) {
     double acc[NV][4];
 #pragma unroll
     for (int q = 0; q < NV; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
-    accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, s, e, kWave, d, lane, acc);
-    if constexpr (LPE < kWave) {
-        if (e - s <= kWave) {  // one run: acc holds fp32 sums, which are added in fp32
-            float a[4] = {(float)acc[0][0], (float)acc[0][1], (float)acc[0][2], (float)acc[0][3]};
-            sum_groups<LPE>(a);
+    accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, (int64_t)s + kWave * wave, e, kWave * kWaves, d, lane,
+                                     acc);
+    // opaque: what derives from the lane below is computed here and not kept
+    // in registers through the gathers
+    asm volatile("" : "+v"(lane));
+    for (int w = 0; w < kWaves; ++w) {  // block-uniform
+        if (w > 0) __syncthreads();
+        if (wave != w) continue;
 #pragma unroll
-            for (int x = 0; x < 4; ++x) acc[0][x] = a[x];
-        } else {
-            sum_groups<LPE>(acc[0]);
+        for (int q = 0; q < NV; ++q)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                if (w > 0) acc[q][x] = red[q * 4 + x][lane] + acc[q][x];
+                if (w < kWaves - 1) red[q * 4 + x][lane] = acc[q][x];
+                __builtin_amdgcn_sched_barrier(0);  // one value at a time: registers, not latency
+            }
+    }
+    if (wave == kWaves - 1) {
+        if constexpr (LPE < kWave) sum_groups<LPE>(acc[0]);
+        store_row<LPE, NV>(yrow, d, lane, acc);
+    }
+    __syncthreads();  // red is reused by the next row
+}
+
+// One launch takes all rows. Row r spans [ptr[r], ptr[r + off]) and is
+// written to row r of Y; kCsr says off == 1 (a CSR row pointer). B and Y point
+// at the first feature of the current slice; d is its width.
+//
+// Blocks from n_long on take kWaves consecutive rows, one wave each. Long
+// rows are a block's work, by one of two ways:
+//   * a list (!kCoop): the first n_long blocks walk the prepared list of long
+//     rows (or the head of `order`), so that the heaviest rows start first;
+//   * kCoop (nothing prepared, n_long = 0): a block that finds long rows among
+//     its own takes them with all its waves when its short rows are done.
+// With `order`, the rows are taken in that order after its first *long_count
+// entries (the long rows). Which block takes a row never changes its sum.
+// (Long rows in a launch of their own before the others left the chip to its
+// last few rows twice, and cost a counter reset per pass. us, two launches /
+// one: 60,013 nodes, mean 27, d = 41, kCoop: 70 / 52; 716,847 nodes, mean 20,
+// d = 512: 4,160 / 4,044; the 30 % slice of 232,965 nodes, mean 490, d = 256:
+// 3,257 / 3,122.)
+template <int LPE, int NV, bool kCsr, bool kHint, bool kBuf, bool kCoop, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void spmm_kernel(
+    const int32_t *__restrict__ ptr, int64_t off, const int32_t *__restrict__ col, const float *__restrict__ val,
+    const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, float *__restrict__ Y, int64_t ldy, int32_t n_rows,
+    int32_t d, int32_t n_long, const int32_t *__restrict__ list, int32_t ordered,
+    const int32_t *__restrict__ long_count) {
+    __shared__ double red[NV * 4][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const auto take_long = [&](int32_t r) {
+        const int32_t s = __builtin_amdgcn_readfirstlane(ptr[r]);
+        const int32_t e = __builtin_amdgcn_readfirstlane(kCsr ? ptr[r + 1] : ptr[(int64_t)r + off]);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // as in take_long_row
+        take_long_row<LPE, NV, kHint, kBuf, kWaves>(col, val, B, ldb, b_bytes, Y + (int64_t)r * ldy, d, s, e, ln,
+                                                    wave, red);
+    };
+    const int32_t bid = blockIdx.x;
+    if constexpr (!kCoop) {
+        if (bid < n_long) {
+            const int32_t n_list = __builtin_amdgcn_readfirstlane(*long_count);
+            for (int32_t j = bid; j < n_list; j += n_long) take_long(__builtin_amdgcn_readfirstlane(list[j]));
+            return;
         }
     }
-    store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
+    const int32_t first = (kCoop ? bid : bid - n_long) * kWaves;  // the block's first row
+    int32_t r = first + wave, s = 0, e = 0;
+    uint32_t longs = 0;  // the block's own long rows
+    if (!kCoop && ordered) {
+        const int64_t i = (int64_t)__builtin_amdgcn_readfirstlane(*long_count) + r;
+        if (i >= n_rows) return;
+        r = __builtin_amdgcn_readfirstlane(list[i]);
+    }
+    if (kCoop && first + kWaves <= n_rows) {
+        // the bounds of all the block's rows, in one round of scalar loads:
+        // every wave finds the same long rows
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+            const int32_t si = ptr[first + i], ei = ptr[(int64_t)first + i + (kCsr ? 1 : off)];
+            if (ei - si > kLongRow) longs |= 1u << i;
+            if (wave == i) s = si, e = ei;
+        }
+    } else {
+        if (kCoop)  // the last block
+            for (int i = 0; first + i < n_rows; ++i)
+                if (ptr[(int64_t)first + i + (kCsr ? 1 : off)] - ptr[first + i] > kLongRow) longs |= 1u << i;
+        if (r < n_rows) {
+            s = __builtin_amdgcn_readfirstlane(ptr[r]);
+            e = __builtin_amdgcn_readfirstlane(kCsr ? ptr[r + 1] : ptr[(int64_t)r + off]);
+        } else if (longs == 0) {
+            return;
+        }
+    }
+    if (r < n_rows && !((kCoop || n_long > 0) && e - s > kLongRow)) {
+        double acc[NV][4];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
+        accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, s, e, kWave, d, lane, acc);
+        if constexpr (LPE < kWave) {
+            if (e - s <= kWave) {  // one run: acc holds fp32 sums, which are added in fp32
+                float a[4] = {(float)acc[0][0], (float)acc[0][1], (float)acc[0][2], (float)acc[0][3]};
+                sum_groups<LPE>(a);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) acc[0][x] = a[x];
+            } else {
+                sum_groups<LPE>(acc[0]);
+            }
+        }
+        store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
+    }
+    if constexpr (kCoop)
+        for (; longs; longs &= longs - 1) take_long(first + __builtin_ctz(longs));  // block-uniform
 }
 
 // Bytes of B that a pass over dl features may read, counted from the first
@@ -560,8 +597,7 @@ constexpr int kClasses = 32;
 
 struct SpmmWs {
     int32_t long_count;  // rows in the long-row list
-    int32_t long_next;   // next long row to hand out (one counter per feature pass)
-    int32_t pad[30];
+    int32_t pad[31];
     int32_t cls_count[kClasses];   // rows per length class (ordered mode)
     int32_t cls_cursor[kClasses];  // next free slot of each class in the order
     int32_t pad2[32];
@@ -569,12 +605,6 @@ struct SpmmWs {
 
 inline int64_t long_rows_bound(int32_t n_rows, int64_t nnz) {
     return std::min<int64_t>(n_rows, nnz / (kLongRow + 1));
-}
-
-// Pieces longer than kLongRow in the column-blocked mode with P ranges: up to
-// P per row, and no more than nnz / (kLongRow + 1) in all.
-inline int64_t long_pieces_bound(int32_t n_rows, int64_t nnz, int32_t P) {
-    return std::min<int64_t>((int64_t)P * n_rows, nnz / (kLongRow + 1));
 }
 
 // Length class of a row: 0 for at most one entry, else ceil(log2(len)), so
@@ -614,7 +644,6 @@ __global__ __launch_bounds__(64) void class_scan_kernel(SpmmWs *h) {
     h->cls_cursor[c] = start;
     if (c == 0) {
         h->long_count = lng;
-        h->long_next = 0;
     }
 }
 
@@ -790,16 +819,8 @@ __global__ __launch_bounds__(256) void combine_blocks_kernel(const float *__rest
 }  // namespace
 
 namespace {
-// entries of the row list: the whole processing order (n_rows), or the long
-// rows, or the long pieces of a column-blocked product with up to kMaxBlocks
-// ranges (one layout for every P, so a workspace never depends on the range
-// count an environment switch picks)
-int64_t list_entries(int32_t n_rows, int64_t nnz) {
-    return std::max<int64_t>({1, (int64_t)n_rows, long_pieces_bound(n_rows, nnz, kMaxBlocks)});
-}
-size_t list_bytes(int32_t n_rows, int64_t nnz) {
-    return align_up(sizeof(int32_t) * (size_t)list_entries(n_rows, nnz), 256);
-}
+// the row list: the whole processing order, or the long rows
+size_t list_bytes(int32_t n_rows) { return align_up(sizeof(int32_t) * (size_t)std::max(n_rows, 1), 256); }
 // bytes of the blocked mode's split points and partial rows for P ranges
 size_t blocked_bytes(int32_t n_rows, int32_t P) {
     if (P <= 1) return 0;
@@ -825,7 +846,7 @@ size_t spmm_ws_bytes(int32_t n_rows, int64_t nnz, int32_t n_cols) {
     size_t blocked = 0;
     for (const int32_t d : {16, 32, kBlockW})  // the three blocked layouts' range counts
         blocked = std::max(blocked, blocked_bytes(n_rows, column_blocks(n_rows, nnz, n_cols, d)));
-    return sizeof(SpmmWs) + list_bytes(n_rows, nnz) + blocked;
+    return sizeof(SpmmWs) + list_bytes(n_rows) + blocked;
 }
 
 int32_t spmm_slice_width(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d) {
@@ -871,33 +892,33 @@ hipError_t spmm_rows_prepare(int32_t n_rows, int64_t nnz_bound, const int32_t *r
         class_scan_kernel<<<1, 64, 0, stream>>>(h);
         class_scatter_kernel<<<cgrid, kCollectThreads, 0, stream>>>(rowptr, n_rows, h, list);
     } else if (lbound > 0) {
-        zero_counters_kernel<<<1, 1, 0, stream>>>(&h->long_count);
-        collect_long_rows_kernel<<<cgrid, kCollectThreads, 0, stream>>>(rowptr, 1, n_rows, &h->long_count, list);
+        zero_count_kernel<<<1, 1, 0, stream>>>(&h->long_count);
+        collect_long_rows_kernel<<<cgrid, kCollectThreads, 0, stream>>>(rowptr, n_rows, &h->long_count, list);
     }
     return hipGetLastError();
 }
 
-hipError_t spmm_blocked_prepare(int32_t n_rows, int64_t nnz_bound, const int32_t *S, int32_t P, void *ws,
-                                hipStream_t stream) {
-    SpmmWs *h = static_cast<SpmmWs *>(ws);
-    int32_t *list = reinterpret_cast<int32_t *>(h + 1);
-    const int32_t nv = P * n_rows;
-    if (P > kMaxBlocks || long_pieces_bound(n_rows, nnz_bound, P) > list_entries(n_rows, nnz_bound))
-        return hipErrorInvalidValue;
-    zero_counters_kernel<<<1, 1, 0, stream>>>(&h->long_count);
-    if (long_rows_bound(n_rows, nnz_bound) > 0 && nv > 0)
-        collect_long_rows_kernel<<<(unsigned)ceil_div(nv, kCollectThreads * kCollectPerThread), kCollectThreads, 0,
-                                   stream>>>(S, n_rows, nv, &h->long_count, list);
-    return hipGetLastError();
-}
+size_t spmm_core_ws_bytes(int32_t n_rows) { return sizeof(SpmmWs) + list_bytes(n_rows); }
 
-size_t spmm_core_ws_bytes(int32_t n_rows, int64_t nnz_bound) { return sizeof(SpmmWs) + list_bytes(n_rows, nnz_bound); }
-
-size_t spmm_blocked_fits(int32_t n_rows, int64_t nnz_bound, int32_t P) {
-    return sizeof(SpmmWs) + list_bytes(n_rows, nnz_bound) + blocked_bytes(n_rows, P);
+size_t spmm_blocked_fits(int32_t n_rows, int32_t P) {
+    return sizeof(SpmmWs) + list_bytes(n_rows) + blocked_bytes(n_rows, P);
 }
 
 const int32_t *spmm_long_count_of(const void *ws) { return &static_cast<const SpmmWs *>(ws)->long_count; }
+
+// Whether a product without a plan lists its long rows first (two launches,
+// about 10 us) or leaves them to the blocks that hold them, whose search for
+// them costs rows of ten entries about 8 % (2,094,669 nodes, mean 10, d = 23:
+// 0.83 ms against 0.75 with the list) and nothing on few rows (60,013 nodes,
+// mean 27, d = 41: 52 us against 70).
+bool spmm_lists_long_rows(int32_t n_rows) { return n_rows >= 262144; }
+
+namespace {
+struct LongRows {
+    int32_t n_long = 0;  // blocks that walk the list
+    int32_t coop = 0;    // no list: the blocks look for their own
+};
+}  // namespace
 
 hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const int32_t *rowptr,
                        const int32_t *col, const float *val, const float *B, int32_t d, int64_t ldb, float *Y,
@@ -911,13 +932,10 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     // rows (the same for the exact product and a full-budget slice of it);
     // it runs only when the workspace holds its buffers.
     int32_t P = column_blocks(n_rows, nnz_hint, n_src_hint, d);
-    const size_t head = sizeof(SpmmWs) + list_bytes(n_rows, nnz_bound);
+    const size_t head = sizeof(SpmmWs) + list_bytes(n_rows);
     if (P > 1 && head + blocked_bytes(n_rows, P) > ws_bytes)  // a fixed scratch may hold the coarser ranges
         P = column_blocks(n_rows, nnz_hint, n_src_hint, d, false);
     if (P > 1 && head + blocked_bytes(n_rows, P) <= ws_bytes) {
-        // the long-piece list must hold every piece the collect pass can find
-        if (P > kMaxBlocks || long_pieces_bound(n_rows, nnz_bound, P) > list_entries(n_rows, nnz_bound))
-            return hipErrorInvalidValue;
         char *p = static_cast<char *>(ws) + head;
         float *part = reinterpret_cast<float *>(p + align_up(sizeof(int32_t) * (size_t)n_rows * (P + 1), 256));
         const int32_t nv = P * n_rows;  // virtual rows, block-major
@@ -926,46 +944,33 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
         const bool pre = prep && prep->ready && prep->P == P && prep->split;
         if (used_prep) *used_prep = pre;
         const int32_t *S = pre ? prep->split : reinterpret_cast<const int32_t *>(p);
-        int32_t n_long;
-        if (pre) {
-            n_long = (int32_t)std::min<int64_t>(
-                prep->long_rows >= 0 ? prep->long_rows : long_rows_bound(n_rows, nnz_bound), kSpmmLongBlocks);
-        } else {
+        if (!pre) {
             const hipError_t e = spmm_split_launch(n_rows, n_cols, rowptr, col, P, reinterpret_cast<int32_t *>(p),
                                                    stream);
             if (e != hipSuccess) return e;
-            // long pieces (a piece of a row longer than kLongRow) go to the
-            // persistent 8-wave blocks as in the unblocked mode
-            n_long = (int32_t)std::min<int64_t>(long_rows_bound(n_rows, nnz_bound), kSpmmLongBlocks);
-            if (n_long > 0) {
-                zero_counters_kernel<<<1, 1, 0, stream>>>(&h->long_count);
-                collect_long_rows_kernel<<<(unsigned)ceil_div(nv, kCollectThreads * kCollectPerThread),
-                                           kCollectThreads, 0, stream>>>(S, n_rows, nv, &h->long_count, list);
-            }
         }
-        const unsigned vgrid = (unsigned)ceil_div(nv, kSpmmRowWaves);
+        // Long pieces (a piece of a row longer than kLongRow) are taken by
+        // the block that holds them, so that they read the same range of B as
+        // their neighbours (from a list, ahead of all ranges: 232,965 nodes,
+        // 490 per row, d = 256: 8.75 ms against 7.66).
+        const int32_t coop = long_rows_bound(n_rows, nnz_bound) > 0 && !(pre && prep->long_rows == 0) ? 1 : 0;
+        const unsigned vgrid = (unsigned)ceil_div(nv, kSpmmWaves);
         // partial rows are W floats apart (the workspace holds kBlockW)
         const int32_t W = blocked_width(d);
         for (int32_t f0 = 0; f0 < d; f0 += W) {
             const int32_t dl = std::min<int32_t>(d - f0, W);
             const uint32_t bb = buffer_bytes(n_cols, ldb, dl);
-#define RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, BUF_)                                                                 \
-    do {                                                                                                      \
-        if (n_long > 0) {                                                                                     \
-            if (f0 > 0 || pre) zero_next_kernel<<<1, 1, 0, stream>>>(&h->long_next);                          \
-            spmm_long_kernel<LPE_, 1, false, BUF_><<<n_long, kSpmmLongWaves * 64, 0, stream>>>(               \
-                S, n_rows, col, val, B + f0, ldb, bb, part, W, dl, &h->long_count, &h->long_next, list);      \
-        }                                                                                                     \
-        spmm_rows_kernel<LPE_, 1, false, false, BUF_><<<vgrid, kSpmmRowWaves * 64, 0, stream>>>(              \
-            S, n_rows, col, val, B + f0, ldb, bb, part, W, nv, dl, n_long > 0 ? 1 : 0, nullptr,               \
-            &h->long_count);                                                                                  \
-    } while (0)
-#define RSC_SPMM_BLOCKED_LAUNCH(LPE_)                  \
-    do {                                               \
-        if (bb != 0)                                   \
-            RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, true);     \
-        else                                           \
-            RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, false);    \
+#define RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, BUF_, COOP_)                                                   \
+    spmm_kernel<LPE_, 1, false, false, BUF_, COOP_, kSpmmWaves><<<vgrid, kSpmmWaves * 64, 0, stream>>>(\
+        S, n_rows, col, val, B + f0, ldb, bb, part, W, nv, dl, 0, nullptr, 0, nullptr)
+#define RSC_SPMM_BLOCKED_LAUNCH(LPE_)                        \
+    do {                                                     \
+        if (bb != 0 && coop)                                 \
+            RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, true, true);     \
+        else if (bb != 0)                                    \
+            RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, true, false);    \
+        else                                                 \
+            RSC_SPMM_BLOCKED_LAUNCH_B(LPE_, false, true);    \
     } while (0)
             if (W == 16)
                 RSC_SPMM_BLOCKED_LAUNCH(4);
@@ -983,54 +988,61 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     }
     const bool ordered = use_order(n_rows, nnz_bound);
     // a plan's row list (long rows, or the whole order) prepared once sits in
-    // this workspace already; else this call builds it
+    // this workspace already; else it is built here, except over few rows,
+    // whose long rows their blocks find
     const bool pre = prep && prep->ready && prep->P == 1 && prep->ordered == ordered;
     if (used_prep) *used_prep = pre;
-    int32_t n_long_blocks;
-    if (pre) {
-        n_long_blocks = (int32_t)std::min<int64_t>(
-            prep->long_rows >= 0 ? prep->long_rows : long_rows_bound(n_rows, nnz_bound), kSpmmLongBlocks);
-    } else {
-        n_long_blocks = (int32_t)std::min<int64_t>(long_rows_bound(n_rows, nnz_bound), kSpmmLongBlocks);
-        const hipError_t e = spmm_rows_prepare(n_rows, nnz_bound, rowptr, ws, stream);
-        if (e != hipSuccess) return e;
+    LongRows lr;
+    if (ordered || (long_rows_bound(n_rows, nnz_bound) > 0 && !(pre && prep->long_rows == 0))) {
+        const bool listed = ordered || (pre ? prep->list : spmm_lists_long_rows(n_rows));
+        if (listed && !pre) {
+            const hipError_t e = spmm_rows_prepare(n_rows, nnz_bound, rowptr, ws, stream);
+            if (e != hipSuccess) return e;
+        }
+        if (!listed)
+            lr.coop = 1;
+        else if (pre && prep->long_rows >= 0)
+            lr.n_long = std::min(prep->long_rows, kSpmmLongBlocksMax);
+        else
+            lr.n_long = (int32_t)std::min<int64_t>(long_rows_bound(n_rows, nnz_bound), kSpmmLongBlocks);
     }
-    const int32_t *order = ordered ? list : nullptr;
-    const unsigned grid = (unsigned)ceil_div(n_rows, kSpmmRowWaves);
     const int32_t slice = spmm_slice_width(n_rows, nnz_hint, n_src_hint, d);
     // the hint pays off only when the gathered rows far outgrow the on-chip
     // caches (MALL included); below that, bypassing them loses reuse
     const bool hint = hint_cols && spmm_hint_taken(n_src_hint, d, slice);
+    const bool wide_blocks = n_rows >= kWideBlockRows && nnz_hint >= (int64_t)kWideBlockMean * n_rows;
     for (int32_t f0 = 0; f0 < d;) {
         const int32_t dl = std::min<int32_t>(d - f0, slice);
         const uint32_t bb = buffer_bytes(n_cols, ldb, dl);
-#define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_, BUF_)                                                         \
-    do {                                                                                               \
-        if (n_long_blocks > 0) {                                                                       \
-            if (f0 > 0 || pre) zero_next_kernel<<<1, 1, 0, stream>>>(&h->long_next);                   \
-            spmm_long_kernel<LPE_, NV_, H_, BUF_><<<n_long_blocks, kSpmmLongWaves * 64, 0, stream>>>(   \
-                rowptr, 1, col, val, B + f0, ldb, bb, Y + f0, ldy, dl, &h->long_count, &h->long_next,  \
-                list);                                                                                 \
-        }                                                                                              \
-        spmm_rows_kernel<LPE_, NV_, true, H_, BUF_><<<grid, kSpmmRowWaves * 64, 0, stream>>>(          \
-            rowptr, 1, col, val, B + f0, ldb, bb, Y + f0, ldy, n_rows, dl, n_long_blocks > 0 ? 1 : 0,  \
-            order, &h->long_count);                                                                    \
+#define RSC_SPMM_LAUNCH_W(LPE_, NV_, H_, BUF_, COOP_, W_)                                              \
+    spmm_kernel<LPE_, NV_, true, H_, BUF_, COOP_, W_>                                                  \
+        <<<(unsigned)(lr.n_long + ceil_div(n_rows, W_)), W_ * 64, 0, stream>>>(                        \
+            rowptr, 1, col, val, B + f0, ldb, bb, Y + f0, ldy, n_rows, dl, lr.n_long, list,            \
+            ordered ? 1 : 0, &h->long_count)
+#define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_, BUF_, W_)                  \
+    do {                                                            \
+        if (lr.coop)                                                \
+            RSC_SPMM_LAUNCH_W(LPE_, NV_, H_, BUF_, true, W_);       \
+        else                                                        \
+            RSC_SPMM_LAUNCH_W(LPE_, NV_, H_, BUF_, false, W_);      \
     } while (0)
-#define RSC_SPMM_LAUNCH_SLICED(LPE_)                     \
-    do {                                                 \
-        if (hint)                                        \
-            RSC_SPMM_LAUNCH_H(LPE_, 1, true, false);     \
-        else if (bb != 0)                                \
-            RSC_SPMM_LAUNCH_H(LPE_, 1, false, true);     \
-        else                                             \
-            RSC_SPMM_LAUNCH_H(LPE_, 1, false, false);    \
+#define RSC_SPMM_LAUNCH_SLICED(LPE_)                                \
+    do {                                                            \
+        if (hint)                                                   \
+            RSC_SPMM_LAUNCH_H(LPE_, 1, true, false, kSpmmWaves);    \
+        else if (bb != 0)                                           \
+            RSC_SPMM_LAUNCH_H(LPE_, 1, false, true, kSpmmWaves);    \
+        else                                                        \
+            RSC_SPMM_LAUNCH_H(LPE_, 1, false, false, kSpmmWaves);   \
     } while (0)
-#define RSC_SPMM_LAUNCH(NV_)                             \
-    do {                                                 \
-        if (hint)                                        \
-            RSC_SPMM_LAUNCH_H(64, NV_, true, false);     \
-        else                                             \
-            RSC_SPMM_LAUNCH_H(64, NV_, false, false);    \
+#define RSC_SPMM_LAUNCH_ROW(H_)                                     \
+    do {                                                            \
+        if (dl > 4 * kWave)                                         \
+            RSC_SPMM_LAUNCH_H(64, 2, H_, false, kSpmmWaves);        \
+        else if (wide_blocks)                                       \
+            RSC_SPMM_LAUNCH_H(64, 1, H_, false, 8);                 \
+        else                                                        \
+            RSC_SPMM_LAUNCH_H(64, 1, H_, false, kSpmmWaves);        \
     } while (0)
         switch (slice) {
             case 16: RSC_SPMM_LAUNCH_SLICED(4); break;
@@ -1038,9 +1050,10 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
             case 64: RSC_SPMM_LAUNCH_SLICED(16); break;
             case 128: RSC_SPMM_LAUNCH_SLICED(32); break;
             default:
-                if (dl <= 4 * kWave) RSC_SPMM_LAUNCH(1); else RSC_SPMM_LAUNCH(2);
+                if (hint) RSC_SPMM_LAUNCH_ROW(true); else RSC_SPMM_LAUNCH_ROW(false);
         }
-#undef RSC_SPMM_LAUNCH
+#undef RSC_SPMM_LAUNCH_ROW
+#undef RSC_SPMM_LAUNCH_W
 #undef RSC_SPMM_LAUNCH_SLICED
 #undef RSC_SPMM_LAUNCH_H
         f0 += dl;

@@ -75,3 +75,45 @@ def test_hinted_layouts(d):
     plan = rsc.SpmmPlan(X)
     assert torch.equal(plan.run(B), rsc.spmm(X, B))
     plan.close()
+
+
+@pytest.mark.parametrize("d", [16, 41, 100, 200, 300])
+def test_long_rows_listed_or_found(d):
+    """Long rows come from a plan's list or are found by the block that holds
+    them, also in the last, partial block: one result, the oracle's."""
+    n_cols = 4000
+    for tail in range(4):   # 0 to 3 rows in the last block, long ones among them
+        lens = np.array([5, 1025, 3, 0, 2, 2000, 1100, 1026] + [1500, 1, 1030][:tail])
+        A = synth.bucket_csr(lens, n_cols, seed=60 + tail)
+        B = synth.dense_normal(n_cols, d, seed=61, ld=(d + 3) // 4 * 4)
+        Bd = torch.from_numpy(B).cuda()
+        X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n_cols)
+        Y = rsc.spmm(X, Bd, d=d)
+        plan = rsc.SpmmPlan(X)
+        assert torch.equal(plan.run(Bd, d=d), Y), (d, tail)
+        plan.close()
+        Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, d=d, with_mag=True)
+        # a 64-entry fp32 chain at most, then fp64
+        assert np.max(np.abs(Y.cpu().numpy().astype(np.float64) - Yo) / np.maximum(S, FLT_MIN)) <= 66 * 2.0 ** -24
+
+
+def test_wide_blocks():
+    """Mean row of 32 entries and 16,384 rows: 8 waves per block, with long
+    rows, against one row fewer (4 waves) and the oracle."""
+    n = 16384
+    lens = np.full(n, 33)
+    lens[[0, 7, 8, 5000, n - 1]] = [1025, 2000, 1030, 1500, 1100]
+    A = synth.bucket_csr(lens, 3000, seed=71)
+    B = synth.dense_normal(3000, 200, seed=72)
+    Bd = torch.from_numpy(B).cuda()
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, 3000)
+    Y = rsc.spmm(X, Bd)
+    plan = rsc.SpmmPlan(X)
+    assert torch.equal(plan.run(Bd), Y)
+    plan.close()
+    m = int(A.rowptr[n - 1])
+    X1 = rsc.DeviceCsr.from_host(A.rowptr[:n], A.col[:m], A.val[:m], 3000)
+    short = torch.from_numpy(np.flatnonzero(lens[:-1] <= 1024)).cuda()
+    assert torch.equal(rsc.spmm(X1, Bd)[short], Y[:-1][short])   # a short row is one wave's in both
+    Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, with_mag=True)
+    assert np.max(np.abs(Y.cpu().numpy().astype(np.float64) - Yo) / np.maximum(S, FLT_MIN)) <= 66 * 2.0 ** -24
