@@ -774,15 +774,12 @@ rsc_status_t rsc_cache_create_ex(const rsc_csr_t *X, const rsc_csr_t *XT, int32_
     return RSC_OK;
 }
 
-// Before a new selection overwrites the mask: keep the current one (if any)
-// as the previous selection, for rsc_cache_staleness.
-static rsc_status_t keep_previous_selection(rsc_cache_t *c, hipStream_t stream) {
-    if (c->version == 0) return RSC_OK;
-    RSC_HIP(hipMemcpyAsync(c->prev_mask, c->mask, sizeof(uint32_t) * (size_t)rsc::ceil_div(c->n, 32),
-                           hipMemcpyDeviceToDevice, stream),
-            "cache previous selection");
+// Where the selection writes the mask words it replaces, for
+// rsc_cache_staleness (nowhere the first time: there is no selection yet).
+static uint32_t *previous_selection(rsc_cache_t *c) {
+    if (c->version == 0) return nullptr;
     c->has_prev = true;
-    return RSC_OK;
+    return c->prev_mask;
 }
 
 // After a new slice: what every sampled product of feature width d (the
@@ -829,12 +826,10 @@ rsc_status_t rsc_cache_select(rsc_cache_t *c, int32_t k, int64_t step, hipStream
     if (k < 0 || k > c->n) return fail(RSC_ERR_INVALID_ARGUMENT, "k = %d outside [0, %d]", k, c->n);
     if (!c->scored) return fail(RSC_ERR_INVALID_ARGUMENT, "cache select before any score");
     RSC_TRY(check_same_device(c->device, "cache"));
-    RSC_TRY(keep_previous_selection(c, stream));
-    RSC_HIP(rsc::topk_launch(c->key, c->n, k, c->idx, c->mask, c->ws_topk, stream), "cache topk");
+    RSC_HIP(rsc::topk_launch(c->key, c->n, k, c->idx, c->mask, c->ws_topk, stream, previous_selection(c)), "cache topk");
     RSC_HIP(rsc::slice_launch(c->X.n_rows, c->X.n_cols, c->X.nnz, c->X.rowptr, c->X.col, c->X.val, c->mask, c->s_rowptr,
-                              c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream),
+                              c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, nullptr, c->h_nnz),
             "cache slice");
-    RSC_HIP(hipMemcpyAsync(c->h_nnz, c->d_nnz, sizeof(int64_t), hipMemcpyDeviceToHost, stream), "cache nnz");
     RSC_HIP(hipEventRecord(c->ev, stream), "cache event");
     c->k = k;
     c->last_step = step;
@@ -853,13 +848,12 @@ rsc_status_t rsc_cache_refresh_random(rsc_cache_t *c, const float *B, int32_t d,
     if (k_draws < 0) return fail(RSC_ERR_INVALID_ARGUMENT, "k_draws < 0");
     RSC_TRY(check_same_device(c->device, "cache"));
     RSC_TRY(rsc_cache_score(c, B, d, ldb, stream));
-    RSC_TRY(keep_previous_selection(c, stream));
-    RSC_HIP(rsc::sample_launch(c->key, c->n, k_draws, seed, c->count, c->colw, c->mask, c->ws_sample, stream),
+    RSC_HIP(rsc::sample_launch(c->key, c->n, k_draws, seed, c->count, c->colw, c->mask, c->ws_sample, stream,
+                               previous_selection(c)),
             "cache sample");
     RSC_HIP(rsc::slice_launch(c->X.n_rows, c->X.n_cols, c->X.nnz, c->X.rowptr, c->X.col, c->X.val, c->mask, c->s_rowptr,
-                              c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, c->colw),
+                              c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, c->colw, c->h_nnz),
             "cache weighted slice");
-    RSC_HIP(hipMemcpyAsync(c->h_nnz, c->d_nnz, sizeof(int64_t), hipMemcpyDeviceToHost, stream), "cache nnz");
     RSC_HIP(hipEventRecord(c->ev, stream), "cache event");
     c->k = k_draws;
     c->last_step = step;

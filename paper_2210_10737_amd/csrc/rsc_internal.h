@@ -79,15 +79,17 @@ hipError_t pair_scores_launch(const double *cn2, const float *B, int32_t n, int3
 
 // ---- top-k -------------------------------------------------------------
 size_t topk_ws_bytes(int32_t n);
+// prev (nullable): receives the mask's words as they were before the call
 hipError_t topk_launch(const uint64_t *key, int32_t n, int32_t k, int32_t *idx, uint32_t *mask,
-                       void *ws, hipStream_t stream);
+                       void *ws, hipStream_t stream, uint32_t *prev = nullptr);
 
 // ---- slice -------------------------------------------------------------
 size_t slice_ws_bytes(int64_t nnz);
+// nnz_host (nullable, pinned host memory): also receives the kept count
 hipError_t slice_launch(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *col,
                         const float *val, const uint32_t *mask, int32_t *rowptr_out,
                         int32_t *col_out, float *val_out, int64_t capacity, int64_t *nnz_out,
-                        void *ws, hipStream_t stream, const double *colw = nullptr);
+                        void *ws, hipStream_t stream, const double *colw = nullptr, int64_t *nnz_host = nullptr);
 
 // ---- column hub hint for the SpMM gathers --------------------------------
 // hub_bits_launch: from per-column degrees (optionally only the columns kept
@@ -104,8 +106,9 @@ hipError_t flag_cols_launch(const int32_t *col, int64_t nnz, const uint32_t *bit
 
 // ---- randomized column-row sampling ------------------------------------
 size_t sample_ws_bytes(int32_t n);
+// prev (nullable): receives the mask's words as they were before the call
 hipError_t sample_launch(const uint64_t *key, int32_t n, int32_t k, uint64_t seed, int32_t *count,
-                         double *colw, uint32_t *mask, void *ws, hipStream_t stream);
+                         double *colw, uint32_t *mask, void *ws, hipStream_t stream, uint32_t *prev = nullptr);
 
 // ---- CSR validation ----------------------------------------------------
 hipError_t csr_validate_launch(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *rowptr,

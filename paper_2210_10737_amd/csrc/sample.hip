@@ -150,7 +150,8 @@ __global__ __launch_bounds__(256) void draw_kernel(const int64_t *__restrict__ W
 
 __global__ __launch_bounds__(256) void colw_kernel(const int32_t *__restrict__ count, const int64_t *__restrict__ w,
                                                    const int64_t *__restrict__ W, int32_t n, int32_t k,
-                                                   double *__restrict__ colw, uint32_t *__restrict__ mask) {
+                                                   double *__restrict__ colw, uint32_t *__restrict__ mask,
+                                                   uint32_t *__restrict__ prev) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & 63;
     const bool in = i < n;
@@ -162,8 +163,11 @@ __global__ __launch_bounds__(256) void colw_kernel(const int32_t *__restrict__ c
     const uint64_t bal = __ballot(c > 0);
     const int64_t word = (i - lane) / 32;
     const int64_t nwords = ((int64_t)n + 31) / 32;
-    if (lane == 0 && word < nwords) mask[word] = (uint32_t)bal;
-    if (lane == 32 && word + 1 < nwords) mask[word + 1] = (uint32_t)(bal >> 32);
+    const int64_t at = word + (lane >> 5);
+    if ((lane & 31) == 0 && at < nwords) {
+        if (prev) prev[at] = mask[at];  // the selection this one replaces
+        mask[at] = (uint32_t)(lane == 0 ? bal : bal >> 32);
+    }
 }
 
 __global__ __launch_bounds__(256) void zero_i32_kernel(int32_t *p, int64_t count) {
@@ -180,7 +184,7 @@ size_t sample_ws_bytes(int32_t n) {
 }
 
 hipError_t sample_launch(const uint64_t *key, int32_t n, int32_t k, uint64_t seed, int32_t *count,
-                         double *colw, uint32_t *mask, void *ws, hipStream_t stream) {
+                         double *colw, uint32_t *mask, void *ws, hipStream_t stream, uint32_t *prev) {
     if (n == 0) return hipSuccess;
     const size_t nn = (size_t)n;
     const int32_t nt = (int32_t)ceil_div(n, kScanTile);
@@ -206,7 +210,7 @@ hipError_t sample_launch(const uint64_t *key, int32_t n, int32_t k, uint64_t see
     tile_scan_kernel<<<1, 1024, 0, stream>>>(tile, nt);
     prefix_kernel<<<nt, 256, 0, stream>>>(w, n, tile, W);
     if (k > 0) draw_kernel<<<(unsigned)ceil_div(k, 256), 256, 0, stream>>>(W, n, k, seed, count);
-    colw_kernel<<<(unsigned)ceil_div(n, 256), 256, 0, stream>>>(count, w, W, n, k, colw, mask);
+    colw_kernel<<<(unsigned)ceil_div(n, 256), 256, 0, stream>>>(count, w, W, n, k, colw, mask, prev);
     return hipGetLastError();
 }
 

@@ -130,21 +130,29 @@ __global__ __launch_bounds__(64) void col_sqnorms_kernel(int32_t n, const int32_
     }
 }
 
-// 256 rows per block, one row per thread. B is streamed through LDS in tiles
-// of 256 rows x 32 features (each row segment is one 128-byte line, read by
+// kRows rows per block, one row per thread. B is streamed through LDS in tiles
+// of kRows rows x 32 features (each row segment is one 128-byte line, read by
 // 8 lanes with 128-bit loads); each thread then sums its own row of the tile
-// in ascending feature order.
-constexpr int kRows = 256;
+// in ascending feature order. Up to kFewRows rows of more than two tiles,
+// one wave per block, so that they spread over the chip (us, 256 rows / 64:
+// 4,096 rows, d = 512: 16.6 / 12.6; 65,536, d = 256: 12.6 / 12.0; but 4,096, d =
+// 64: 3.9 / 4.7); else 256 rows.
+//
+// Rows that are not whole lines (ld % 32 != 0) straddle two: their lines are
+// read by two tiles, the second time from L2, so they are loaded with the
+// default policy (716,847 rows, d = 100: 88.6 us non-temporally, 76.3 so).
+constexpr int32_t kFewRows = 65536;
 constexpr int kTileF = 32;
 typedef float vf4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void pair_scores_kernel(const double *__restrict__ cn2,
+template <int kRows, bool kNt>
+__global__ __launch_bounds__(kRows) void pair_scores_kernel(const double *__restrict__ cn2,
                                                           const float *__restrict__ B, int32_t n,
                                                           int32_t d, int64_t ldb,
                                                           uint64_t *__restrict__ key,
                                                           float *__restrict__ score,
                                                           double *__restrict__ rn2) {
-    constexpr int kLoads = kRows * kTileF / 4 / 256;  // float4 loads per thread per tile
+    constexpr int kLoads = kTileF / 4;  // float4 loads per thread per tile
     __shared__ float tile[kRows][kTileF + 1];
     const int t = threadIdx.x;
     const int64_t row0 = (int64_t)blockIdx.x * kRows;
@@ -153,15 +161,16 @@ __global__ __launch_bounds__(256) void pair_scores_kernel(const double *__restri
     auto load = [&](int32_t f0) {
 #pragma unroll
         for (int it = 0; it < kLoads; ++it) {
-            const int idx = t + 256 * it;
+            const int idx = t + kRows * it;
             const int rl = idx >> 3, fq = idx & 7;
             const int64_t row = row0 + rl;
             const int32_t f = f0 + 4 * fq;
             v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
             // ld % 4 == 0 and ld >= d, so a float4 starting below d stays in the row;
-            // B is read once, so its lines are streamed past the caches
+            // whole lines are read once and streamed past the caches (kNt)
             if (row < n && f < d) {
-                const vf4 x = __builtin_nontemporal_load(reinterpret_cast<const vf4 *>(B + row * ldb + f));
+                const vf4 *p = reinterpret_cast<const vf4 *>(B + row * ldb + f);
+                const vf4 x = kNt ? __builtin_nontemporal_load(p) : *p;
                 v[it] = make_float4(x.x, x.y, x.z, x.w);
             }
         }
@@ -171,7 +180,7 @@ __global__ __launch_bounds__(256) void pair_scores_kernel(const double *__restri
     for (int32_t f0 = 0; f0 < d; f0 += kTileF) {
 #pragma unroll
         for (int it = 0; it < kLoads; ++it) {
-            const int idx = t + 256 * it;
+            const int idx = t + kRows * it;
             const int rl = idx >> 3, fq = idx & 7;
             tile[rl][4 * fq + 0] = v[it].x;
             tile[rl][4 * fq + 1] = v[it].y;
@@ -223,12 +232,13 @@ __global__ __launch_bounds__(kSumThreads) void sum_chunks_kernel(const double *_
                                                                  double *__restrict__ part) {
     __shared__ double lds[kSumThreads];
     const int64_t base = (int64_t)blockIdx.x * kSumChunk + threadIdx.x;
+    double v[kSumPer];  // all loads before the chain of adds
+#pragma unroll
+    for (int j = 0; j < kSumPer; ++j) v[j] = x[std::min<int64_t>(base + (int64_t)kSumThreads * j, n - 1)];
     double acc = 0.0;
 #pragma unroll
-    for (int j = 0; j < kSumPer; ++j) {
-        const int64_t i = base + (int64_t)kSumThreads * j;
-        if (i < n) acc += x[i];
-    }
+    for (int j = 0; j < kSumPer; ++j)
+        if (base + (int64_t)kSumThreads * j < n) acc += v[j];
     const double s = block_tree_sum(acc, lds);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
@@ -248,6 +258,10 @@ size_t sum_ws_bytes(int64_t n) { return sizeof(double) * (size_t)std::max<int64_
 
 hipError_t sum_fixed_order_launch(const double *x, int64_t n, double *ws, double *out, hipStream_t stream) {
     const int64_t np = ceil_div(n, kSumChunk);
+    if (np == 1) {  // one block's sum is the total (adding it to zeros changes nothing)
+        sum_chunks_kernel<<<1, kSumThreads, 0, stream>>>(x, n, out);
+        return hipGetLastError();
+    }
     if (np > 0) sum_chunks_kernel<<<(unsigned)np, kSumThreads, 0, stream>>>(x, n, ws);
     sum_parts_kernel<<<1, kSumThreads, 0, stream>>>(ws, np, out);
     return hipGetLastError();
@@ -263,7 +277,16 @@ hipError_t col_sqnorms_launch(int32_t n, const int32_t *rowptr_t, const float *v
 hipError_t pair_scores_launch(const double *cn2, const float *B, int32_t n, int32_t d, int64_t ldb,
                               uint64_t *key, float *score, double *rn2, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    pair_scores_kernel<<<(unsigned)ceil_div(n, kRows), 256, 0, stream>>>(cn2, B, n, d, ldb, key, score, rn2);
+    const bool nt = ldb % kTileF == 0;
+#define RSC_SCORES(ROWS_, NT_)                                                                             \
+    pair_scores_kernel<ROWS_, NT_><<<(unsigned)ceil_div(n, ROWS_), ROWS_, 0, stream>>>(cn2, B, n, d, ldb, \
+                                                                                       key, score, rn2)
+    if (n <= kFewRows && d > 2 * kTileF) {
+        if (nt) RSC_SCORES(64, true); else RSC_SCORES(64, false);
+    } else {
+        if (nt) RSC_SCORES(256, true); else RSC_SCORES(256, false);
+    }
+#undef RSC_SCORES
     return hipGetLastError();
 }
 

@@ -9,13 +9,14 @@
 //   0. per tile of 4096 entries: the first row whose Rowptr lies in it (a
 //      table built from Rowptr; it also clears the tile counts);
 //   1. per tile: the kept flags as 64 wave ballots (reads col; the n-bit mask
-//      is tested from LDS, loaded piece by piece), stored for step 3, and
-//      their count;
-//   2. one block scans the tile counts (and stores nnz');
-//   3. per tile: load col/val into registers, scan the tile's ballot counts,
-//      compact the kept entries in LDS and write them out coalesced at their
-//      global positions, and write Rowptr'[i] for every row whose Rowptr[i]
-//      falls in the tile.
+//      is tested from LDS, loaded piece by piece), stored for step 2, and
+//      their count (then a launch adds the counts of 256 tiles each);
+//   2. per tile: load col/val into registers, add the counts of the tiles
+//      before it, scan the tile's ballot counts, compact the kept entries in
+//      LDS and write them out coalesced at their global positions, and write
+//      Rowptr'[i] for every row whose Rowptr[i] falls in the tile; the last
+//      tile stores nnz'.
+// A small operand takes steps 0 and 1 in one launch.
 // A single-pass form (count, decoupled look-back scan over ticketed tiles,
 // compaction in one kernel; below) gives the same bytes and is available on
 // request; the launches above measured faster.
@@ -30,6 +31,7 @@ namespace {
 
 constexpr int kTile = 4096;          // entries per tile
 constexpr int kPer = kTile / 256;    // 256-entry chunks per tile
+constexpr int kCoarse = 256;         // tiles per coarse count
 
 // Entry o of a tile (0 <= o < kTile) is position o & 255 of chunk o >> 8;
 // within a chunk, wave (o >> 6) & 3, lane o & 63. The kept flags of one
@@ -149,6 +151,20 @@ __global__ __launch_bounds__(kCountThreads) void slice_count_kernel(const int32_
     }
 }
 
+// Marks the tiles whose first row is one of first, first + stride, ...
+// (<= n_rows): row i takes the tiles whose first entry lies in
+// (rowptr[i - 1], rowptr[i]] (rowptr[-1] read as -1).
+__device__ __forceinline__ void mark_tile_rows(const int32_t *__restrict__ rowptr, int32_t n_rows, int32_t nt,
+                                               int64_t first, int64_t stride, int32_t *__restrict__ tile_row) {
+    for (int64_t i = first; i <= n_rows; i += stride) {
+        const int64_t a = i == 0 ? -1 : (int64_t)rowptr[i - 1];
+        const int64_t b = rowptr[i];
+        const int64_t t0 = a < 0 ? 0 : a / kTile + 1;  // first tile starting above a
+        const int64_t t1 = min<int64_t>(b / kTile, (int64_t)nt - 1);
+        for (int64_t t = t0; t <= t1; ++t) tile_row[t] = (int32_t)i;
+    }
+}
+
 // tile_row[t] = the first row i with rowptr[i] >= t * kTile, for every tile
 // t < nt: row i takes the tiles whose first entry lies in
 // (rowptr[i - 1], rowptr[i]] (rowptr[-1] read as -1), so for a well-formed
@@ -165,40 +181,71 @@ __global__ __launch_bounds__(256) void slice_tile_rows_kernel(const int32_t *__r
     for (int64_t t = first; t < nt; t += stride) tile_cnt[t] = 0;
     if (tile_bits_to_clear)
         for (int64_t t = first; t < (int64_t)nt * kGroups; t += stride) tile_bits_to_clear[t] = 0;
-    for (int64_t i = first; i <= n_rows; i += stride) {
-        const int64_t a = i == 0 ? -1 : (int64_t)rowptr[i - 1];
-        const int64_t b = rowptr[i];
-        const int64_t t0 = a < 0 ? 0 : a / kTile + 1;  // first tile starting above a
-        const int64_t t1 = min<int64_t>(b / kTile, (int64_t)nt - 1);
-        for (int64_t t = t0; t <= t1; ++t) tile_row[t] = (int32_t)i;
-    }
+    mark_tile_rows(rowptr, n_rows, nt, first, stride, tile_row);
 }
 
-__global__ __launch_bounds__(1024) void slice_scan_kernel(int32_t nt, const uint32_t *__restrict__ tile_cnt,
-                                                          uint32_t *__restrict__ tile_off,
-                                                          int64_t *__restrict__ nnz_out) {
-    __shared__ int64_t sh[1024];
-    const int t = threadIdx.x;
-    const int32_t per = (nt + 1023) / 1024;
-    const int32_t lo = min(nt, t * per), hi = min(nt, lo + per);
-    int64_t s = 0;
-#pragma unroll 8
-    for (int32_t i = lo; i < hi; ++i) s += tile_cnt[i];  // unrolled: 8 loads in flight, not 1
-    sh[t] = s;
+// coarse_cnt[c] = kept entries of tiles [c kCoarse, (c + 1) kCoarse), and each
+// tile's count becomes the kept entries before it within them: with these, an
+// emit block finds its place from one word and at most nt / kCoarse others. (A
+// scan of all tiles by one block took 22 us on 30,812 tiles; adding the coarse
+// counts by atomics in the count pass made it 1 ms slower, all its waves
+// hitting a few words.)
+__global__ __launch_bounds__(kCoarse) void slice_coarse_kernel(uint32_t *__restrict__ tile_cnt, int32_t nt,
+                                                               uint32_t *__restrict__ coarse_cnt) {
+    __shared__ uint32_t s[kCoarse / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int32_t t = blockIdx.x * kCoarse + threadIdx.x;
+    const uint32_t c = t < nt ? tile_cnt[t] : 0u;
+    uint32_t incl = c;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t x = __shfl_up(incl, off);
+        if (lane >= off) incl += x;
+    }
+    if (lane == 63) s[w] = incl;
     __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const int64_t x = t >= off ? sh[t - off] : 0;
-        __syncthreads();
-        sh[t] += x;
-        __syncthreads();
+    for (int u = 0; u < w; ++u) incl += s[u];
+    if (t < nt) tile_cnt[t] = incl - c;
+    if (threadIdx.x == kCoarse - 1) coarse_cnt[blockIdx.x] = incl;
+}
+
+// Small operands (the mask stays in L1 and the tiles are few): one block per
+// tile tests its entries against the mask in global memory and stores its
+// count, with nothing to clear beforehand; every block also marks its share of
+// the tile rows. One launch in place of two.
+constexpr int32_t kSmallWords = 4096;  // 131,072 columns
+constexpr int32_t kSmallTiles = 2048;
+
+__global__ __launch_bounds__(256) void slice_count_small_kernel(const int32_t *__restrict__ rowptr, int32_t n_rows,
+                                                                const int32_t *__restrict__ col, int64_t nnz,
+                                                                const uint32_t *__restrict__ mask, int32_t n_words,
+                                                                int32_t nt, int32_t *__restrict__ tile_row,
+                                                                uint32_t *__restrict__ tile_cnt,
+                                                                uint64_t *__restrict__ tile_bits) {
+    __shared__ uint64_t s_ball[kGroups];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int64_t ts = (int64_t)blockIdx.x * kTile;
+    const int32_t cnt = (int32_t)min<int64_t>(kTile, nnz - ts);
+    int32_t c[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) c[j] = 256 * j + t < cnt ? col[ts + 256 * j + t] : -1;
+    mark_tile_rows(rowptr, n_rows, nt, (int64_t)blockIdx.x * 256 + t, (int64_t)gridDim.x * 256, tile_row);
+    uint32_t word[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) word[j] = mask[min((uint32_t)c[j] >> 5, (uint32_t)(n_words - 1))];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const bool k = c[j] >= 0 && c[j] >> 5 < n_words && ((word[j] >> (c[j] & 31)) & 1u);
+        const uint64_t b = __ballot(k);
+        if (lane == 0) s_ball[j * 4 + w] = b;
     }
-    int64_t run = sh[t] - s;
-#pragma unroll 8
-    for (int32_t i = lo; i < hi; ++i) {
-        tile_off[i] = (uint32_t)run;
-        run += tile_cnt[i];
+    __syncthreads();
+    if (w == 0) {
+        const uint64_t b = s_ball[lane];
+        tile_bits[(int64_t)blockIdx.x * kGroups + lane] = b;
+        uint32_t sum = __popcll(b);
+        for (int m = 32; m > 0; m >>= 1) sum += __shfl_xor(sum, m);
+        if (lane == 0) tile_cnt[blockIdx.x] = sum;
     }
-    if (t == 1023) *nnz_out = sh[1023];
 }
 
 // First index i in [0, n] with rowptr[i] >= x (rowptr has n + 1 entries).
@@ -217,17 +264,20 @@ __global__ __launch_bounds__(256) void slice_emit_kernel(const int32_t *__restri
                                                          const int32_t *__restrict__ col,
                                                          const float *__restrict__ val, int64_t nnz,
                                                          const uint64_t *__restrict__ tile_bits,
-                                                         const uint32_t *__restrict__ tile_off,
+                                                         const uint32_t *__restrict__ tile_cnt,
+                                                         const uint32_t *__restrict__ coarse_cnt,
                                                          const int32_t *__restrict__ tile_row,
                                                          int32_t *__restrict__ rowptr_out,
                                                          int32_t *__restrict__ col_out,
                                                          float *__restrict__ val_out, int64_t capacity,
+                                                         int64_t *__restrict__ nnz_out, int64_t *nnz_host,
                                                          const double *__restrict__ colw) {
     __shared__ int32_t s_col[kTile];   // kept entries of the tile, compacted
     __shared__ float s_val[kTile];
     __shared__ uint64_t s_ball[kGroups];
     __shared__ uint32_t s_pre[kGroups + 1];  // kept entries before each ballot; [kGroups] = tile total
     __shared__ int32_t s_rows[2];
+    __shared__ int64_t s_before[4];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int64_t ts = (int64_t)blockIdx.x * kTile;
     const int64_t te = min<int64_t>(ts + kTile, nnz);
@@ -236,6 +286,14 @@ __global__ __launch_bounds__(256) void slice_emit_kernel(const int32_t *__restri
     // so a malformed row pointer cannot send the stores below out of range)
     if (t == 0) s_rows[0] = min(max(tile_row[blockIdx.x], 0), n_rows + 1);
     if (t == 1) s_rows[1] = last ? n_rows + 1 : min(max(tile_row[blockIdx.x + 1], 0), n_rows + 1);
+    // Kept entries before this tile: its place in its group of tiles plus the
+    // groups before it; or (no coarse counts) the counts of all tiles before
+    // it. Loaded ahead of col and val: loads return in order.
+    const uint32_t *before = coarse_cnt ? coarse_cnt : tile_cnt;
+    const int32_t n_before = coarse_cnt ? blockIdx.x / kCoarse : blockIdx.x;
+    const uint32_t before0 = t < n_before ? before[t] : 0u;
+    const uint32_t in_group = coarse_cnt ? tile_cnt[blockIdx.x] : 0u;
+    const uint64_t my_ball = tile_bits[(int64_t)blockIdx.x * kGroups + lane];
     int32_t rc[kPer];
     float rv[kPer];
     uint64_t ball[kPer];
@@ -245,7 +303,13 @@ __global__ __launch_bounds__(256) void slice_emit_kernel(const int32_t *__restri
         rc[j] = p < te ? __builtin_nontemporal_load(col + p) : -1;
         rv[j] = p < te ? __builtin_nontemporal_load(val + p) : 0.f;
     }
-    if (t < kGroups) s_ball[t] = tile_bits[(int64_t)blockIdx.x * kGroups + t];
+    if (t < kGroups) s_ball[t] = my_ball;
+    {
+        int64_t v = before0;
+        for (int32_t i = t + 256; i < n_before; i += 256) v += before[i];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
+        if (lane == 0) s_before[w] = v;
+    }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kPer; ++j) ball[j] = s_ball[j * 4 + w];
@@ -270,8 +334,12 @@ __global__ __launch_bounds__(256) void slice_emit_kernel(const int32_t *__restri
         }
     }
     __syncthreads();
-    const int64_t base = (int64_t)tile_off[blockIdx.x];
+    const int64_t base = s_before[0] + s_before[1] + s_before[2] + s_before[3] + in_group;
     const uint32_t total = s_pre[kGroups];
+    if (last && t == 0) {
+        *nnz_out = base + total;
+        if (nnz_host) __hip_atomic_store(nnz_host, base + total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     for (uint32_t i = t; i < total; i += 256) {
         const int64_t pos = base + i;
         if (pos < capacity) {
@@ -473,11 +541,14 @@ __global__ __launch_bounds__(256) void zero_words_kernel(uint64_t *__restrict__ 
 }
 
 __global__ __launch_bounds__(256) void zero_rows_kernel(int32_t *__restrict__ p, int64_t count,
-                                                        int64_t *__restrict__ nnz_out) {
+                                                        int64_t *__restrict__ nnz_out, int64_t *nnz_host) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *nnz_out = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *nnz_out = 0;
+        if (nnz_host) __hip_atomic_store(nnz_host, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // Whether the fused kernel keeps the mask in LDS: a copy per block, when at
@@ -486,12 +557,12 @@ bool mask_in_lds(int32_t n_words) {
     return sizeof(uint32_t) * (size_t)n_words + 2048 <= (size_t)kLdsPerCu / 3;
 }
 
-// The three launches are the default: with the count's ballots and counts
+// The launches are the default: with the count's ballots and counts
 // published by atomics and the emit's row ranges read from a table, they
 // measured faster than the single pass on every workload (slice kernels,
-// three launches against single pass: tiny 21 / 26 us, social 344-393 /
-// 372-403 us, protein 250 / 281 us, gcn2 72 / 114 us, copurchase 503 /
-// 787 us). RSC_SLICE_FUSED = 1 / 0 forces the single-pass / three-launch form.
+// launches against single pass: tiny 11 / 26 us, social 344-393 /
+// 372-403 us, protein 219 / 281 us, gcn2 72 / 114 us, copurchase 388 /
+// 787 us). RSC_SLICE_FUSED = 1 / 0 forces the single-pass / multi-launch form.
 // RSC_SLICE_PAIRED = 0 makes a two-piece mask walk col twice with one block
 // per CU instead of in pairs.
 bool paired_count() {
@@ -508,25 +579,27 @@ bool use_fused() {
 
 size_t slice_ws_bytes(int64_t nnz) {
     const size_t nt = (size_t)ceil_div(std::max<int64_t>(nnz, 1), kTile);
-    return 2 * align_up(nt * sizeof(uint32_t), 256) + align_up(nt * kGroups * sizeof(uint64_t), 256) +
+    return align_up(nt * sizeof(uint32_t), 256) + align_up((size_t)ceil_div((int64_t)nt, kCoarse) * sizeof(uint32_t), 256) +
+           align_up(nt * kGroups * sizeof(uint64_t), 256) +
            align_up((nt + 1) * sizeof(int32_t), 256);
 }
 
 hipError_t slice_launch(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *col,
                         const float *val, const uint32_t *mask, int32_t *rowptr_out,
                         int32_t *col_out, float *val_out, int64_t capacity, int64_t *nnz_out,
-                        void *ws, hipStream_t stream, const double *colw) {
+                        void *ws, hipStream_t stream, const double *colw, int64_t *nnz_host) {
     if (nnz == 0) {
         zero_rows_kernel<<<(unsigned)std::min<int64_t>(ceil_div((int64_t)n_rows + 1, 256), 1024), 256, 0,
-                           stream>>>(rowptr_out, (int64_t)n_rows + 1, nnz_out);
+                           stream>>>(rowptr_out, (int64_t)n_rows + 1, nnz_out, nnz_host);
         return hipGetLastError();
     }
     const int32_t nt = (int32_t)ceil_div(nnz, kTile);
     const size_t tb = align_up((size_t)nt * sizeof(uint32_t), 256);
     uint32_t *tile_cnt = static_cast<uint32_t *>(ws);
-    uint32_t *tile_off = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + tb);
-    uint64_t *tile_bits = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) + 2 * tb);
-    int32_t *tile_row = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + 2 * tb +
+    const size_t cb = align_up((size_t)ceil_div(nt, kCoarse) * sizeof(uint32_t), 256);
+    uint32_t *coarse_cnt = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + tb);
+    uint64_t *tile_bits = reinterpret_cast<uint64_t *>(static_cast<char *>(ws) + tb + cb);
+    int32_t *tile_row = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + tb + cb +
                                                     align_up((size_t)nt * kGroups * sizeof(uint64_t), 256));
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
@@ -553,6 +626,17 @@ hipError_t slice_launch(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32
             slice_fused_kernel<false, kFusedSub><<<grid, kFusedThreads, 0, stream>>>(
                 rowptr, n_rows, col, val, nnz, mask, n_words, nt2, status, ticket, rowptr_out, col_out, val_out,
                 capacity, nnz_out, ticket + 1, colw);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || !nnz_host) return e;
+        return hipMemcpyAsync(nnz_host, nnz_out, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
+    }
+    const bool small = n_words > 0 && n_words <= kSmallWords && nt <= kSmallTiles;
+    if (small) {
+        slice_count_small_kernel<<<nt, 256, 0, stream>>>(rowptr, n_rows, col, nnz, mask, n_words, nt, tile_row,
+                                                         tile_cnt, tile_bits);
+        slice_emit_kernel<<<nt, 256, 0, stream>>>(rowptr, n_rows, col, val, nnz, tile_bits, tile_cnt, nullptr,
+                                                  tile_row, rowptr_out, col_out, val_out, capacity, nnz_out, nnz_host,
+                                                  colw);
         return hipGetLastError();
     }
     // a mask of two LDS pieces is tested by pairs of blocks (one piece each,
@@ -572,9 +656,9 @@ hipError_t slice_launch(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32
         slice_count_kernel<false, kTilesPerIterSingle><<<cgrid, kCountThreads, 0, stream>>>(
             col, nnz, mask, n_words, nt, tile_cnt, tile_bits);
     }
-    slice_scan_kernel<<<1, 1024, 0, stream>>>(nt, tile_cnt, tile_off, nnz_out);
-    slice_emit_kernel<<<nt, 256, 0, stream>>>(rowptr, n_rows, col, val, nnz, tile_bits, tile_off, tile_row,
-                                              rowptr_out, col_out, val_out, capacity, colw);
+    slice_coarse_kernel<<<(unsigned)ceil_div(nt, kCoarse), kCoarse, 0, stream>>>(tile_cnt, nt, coarse_cnt);
+    slice_emit_kernel<<<nt, 256, 0, stream>>>(rowptr, n_rows, col, val, nnz, tile_bits, tile_cnt, coarse_cnt, tile_row,
+                                              rowptr_out, col_out, val_out, capacity, nnz_out, nnz_host, colw);
     return hipGetLastError();
 }
 

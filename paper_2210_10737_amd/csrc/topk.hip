@@ -11,20 +11,27 @@
 //    the state after it, one slot per pass, so no kernel of its own is
 //    needed. After the last pass T is known, and r = the number of keys
 //    equal to T that must be kept (G = k - r keys are strictly above T).
-// 2. Tiles of 4096 keys count (== T) and (> T) (their kernel makes the last
-//    pick); one block scans the tile counts; a third kernel keeps key i iff
-//    key > T, or key == T and fewer than r equal keys precede it, writing
-//    mask words from wave ballots and idx at the running count of kept keys.
-//    Everything is integer, so the result is exact and deterministic.
+//    A pick whose bin is wanted whole (as many keys as remain to be taken,
+//    a single one as a rule after three digits) ends the search: the digits
+//    below are left out of every comparison, and the remaining passes return
+//    without reading a key.
+// 2. Tiles of keys count (== T) and (> T) (their kernel makes the last pick);
+//    the next kernel adds the counts of the tiles before its own and keeps key
+//    i iff key > T, or key == T and fewer than r equal keys precede it,
+//    writing mask words from wave ballots and idx at the running count of kept
+//    keys. Everything is integer, so the result is exact and deterministic.
 // Up to 16,384 keys the whole selection runs in one block with the keys in
-// LDS (one launch; the small graphs are launch-bound).
+// registers (one launch; the small graphs are launch-bound).
+//
+// Bound by launches: 9 dependent ones of 2 to 10 us each. us, every pass over
+// all keys and a scan of its own / this form: 2,449,029 keys 101 / 80; 132,534
+// keys 61 / 45; 4,096 keys (one launch) 25.6 / 8.7.
 #include "rsc_internal.h"
 
 namespace rsc {
 namespace {
 
 constexpr int kBins = 2048;
-constexpr int kTile = 4096;     // keys per tile: 4 waves x 16 groups of 64
 constexpr int kPasses = 6;
 
 // Of eq keys equal to the threshold, how many are taken when want more are
@@ -40,7 +47,7 @@ struct TopkState {
     uint64_t prefix;  // digits of T fixed so far
     uint64_t pmask;   // which bits of prefix are fixed
     int64_t k_rem;    // how many keys among those matching prefix remain to be taken
-    int64_t pad;
+    int64_t done;     // all of them: no further digit matters
 };
 
 // st[p] = the state after p picks (st[0] initial, st[kPasses] final: prefix
@@ -53,17 +60,24 @@ struct TopkWs {
 
 struct PickOut {
     uint64_t prefix, pmask;
-    int64_t k_rem, count;
+    int64_t k_rem, done;
 };
 
 // One block of 256 threads picks the digit of `pass` from histogram h,
 // starting from state *sp: thread t owns the bins nb-1-t*per .. nb-per-t*per
 // (descending), and an exclusive scan over threads (within each wave by
 // shuffles, then over the four wave totals) gives the count of keys in
-// higher bins. Every thread gets the new state.
-__device__ void block_pick_256(const TopkState *sp, const uint32_t *h, int pass, uint64_t &prefix, uint64_t &pmask,
+// higher bins. Every thread gets the new state; a search that is done keeps
+// its state. True if it is done.
+__device__ bool block_pick_256(const TopkState *sp, const uint32_t *h, int pass, uint64_t &prefix, uint64_t &pmask,
                                int64_t &k_rem, int64_t *wsum, PickOut *s_out) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (sp->done) {  // uniform
+        prefix = sp->prefix;
+        pmask = sp->pmask;
+        k_rem = sp->k_rem;
+        return true;
+    }
     const int shift = kShift[pass];
     const int nb = 1 << kWidth[pass];
     const int per = nb / 256;  // 8 or 4
@@ -93,6 +107,7 @@ __device__ void block_pick_256(const TopkState *sp, const uint32_t *h, int pass,
             s_out->prefix = prefix | ((uint64_t)b << shift);
             s_out->pmask = pmask | ((uint64_t)(nb - 1) << shift);
             s_out->k_rem = k_rem - run;
+            s_out->done = c == k_rem - run;
         }
         run += c;
     }
@@ -100,6 +115,7 @@ __device__ void block_pick_256(const TopkState *sp, const uint32_t *h, int pass,
     prefix = s_out->prefix;
     pmask = s_out->pmask;
     k_rem = s_out->k_rem;
+    return s_out->done != 0;
 }
 
 __global__ __launch_bounds__(256) void topk_init_kernel(TopkWs *h, int64_t k) {
@@ -108,6 +124,7 @@ __global__ __launch_bounds__(256) void topk_init_kernel(TopkWs *h, int64_t k) {
         h->st[0].prefix = 0;
         h->st[0].pmask = 0;
         h->st[0].k_rem = k;
+        h->st[0].done = 0;
     }
 }
 
@@ -135,12 +152,15 @@ __global__ __launch_bounds__(256) void topk_hist_kernel(const uint64_t *__restri
     uint64_t prefix = ws->st[0].prefix, pmask = ws->st[0].pmask;
     if (pass > 0) {
         int64_t k_rem;
-        block_pick_256(&ws->st[pass - 1], ws->hist[(pass - 1) % 3], pass - 1, prefix, pmask, k_rem, wsum, &s_out);
+        const bool done = block_pick_256(&ws->st[pass - 1], ws->hist[(pass - 1) % 3], pass - 1, prefix, pmask, k_rem,
+                                         wsum, &s_out);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             ws->st[pass].prefix = prefix;
             ws->st[pass].pmask = pmask;
             ws->st[pass].k_rem = k_rem;
+            ws->st[pass].done = done;
         }
+        if (done) return;  // grid-uniform; no later pass reads a histogram
     }
     if (blockIdx.x == 0)
         for (int b = threadIdx.x; b < kBins; b += blockDim.x) ws->hist[(pass + 1) % 3][b] = 0;
@@ -182,7 +202,8 @@ __global__ __launch_bounds__(256) void topk_hist_kernel(const uint64_t *__restri
 }
 
 // Also makes the last pass's pick (every block; the first records the final
-// state, T and r, for the scan and the emit).
+// state, T and r, for the emit). kPer keys per thread, 256 kPer per tile.
+template <int kPer>
 __global__ __launch_bounds__(256) void topk_tile_count_kernel(const uint64_t *__restrict__ key,
                                                               int32_t n, TopkWs *ws,
                                                               uint32_t *__restrict__ tile_eq,
@@ -191,13 +212,10 @@ __global__ __launch_bounds__(256) void topk_tile_count_kernel(const uint64_t *__
     __shared__ int64_t wsum[4];
     __shared__ PickOut s_out;
     // the tile's keys are loaded before the pick, so the two waits overlap
-    const int64_t ts = (int64_t)blockIdx.x * kTile;
-    uint64_t kv[kTile / 256];
+    const int64_t ts = (int64_t)blockIdx.x * 256 * kPer;
+    uint64_t kv[kPer];
 #pragma unroll
-    for (int j = 0; j < kTile / 256; ++j) {
-        const int64_t i = ts + threadIdx.x + 256 * j;
-        kv[j] = i < n ? key[i] : 0ull;
-    }
+    for (int j = 0; j < kPer; ++j) kv[j] = key[std::min<int64_t>(ts + threadIdx.x + 256 * j, n - 1)];
     uint64_t T, pmask;
     int64_t r;
     block_pick_256(&ws->st[kPasses - 1], ws->hist[(kPasses - 1) % 3], kPasses - 1, T, pmask, r, wsum, &s_out);
@@ -208,10 +226,10 @@ __global__ __launch_bounds__(256) void topk_tile_count_kernel(const uint64_t *__
     }
     uint32_t eq = 0, gt = 0;
 #pragma unroll
-    for (int j = 0; j < kTile / 256; ++j) {
+    for (int j = 0; j < kPer; ++j) {
         const bool in = ts + threadIdx.x + 256 * j < n;
-        eq += in && kv[j] == T;
-        gt += in && kv[j] > T;
+        eq += in && (kv[j] & pmask) == T;
+        gt += in && (kv[j] & pmask) > T;
     }
     for (int off = 32; off > 0; off >>= 1) {
         eq += __shfl_down(eq, off);
@@ -226,236 +244,264 @@ __global__ __launch_bounds__(256) void topk_tile_count_kernel(const uint64_t *__
     }
 }
 
-// Block-wide exclusive scan (1024 threads, values int64): within each wave
-// by shuffles, then over the 16 wave totals (sh holds at least 16 entries).
-__device__ int64_t block_exclusive_scan_1024(int64_t v, int64_t *sh, int64_t *total) {
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    int64_t incl = v;
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t x = __shfl_up(incl, off);
-        if (lane >= off) incl += x;
-    }
-    if (lane == 63) sh[w] = incl;
+// Sum of x[0 .. m) by a block of 256 threads; every thread gets it. sh holds
+// four entries and may be reused after the caller's next barrier.
+__device__ __forceinline__ int64_t block_sum_256(const uint32_t *__restrict__ x, int32_t m, int64_t *sh) {
+    int64_t v = 0;
+#pragma unroll 4
+    for (int32_t i = threadIdx.x; i < m; i += 256) v += x[i];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    int64_t before = 0, tot = 0;
-    for (int u = 0; u < 16; ++u) {
-        const int64_t x = sh[u];
-        before += u < w ? x : 0;
-        tot += x;
-    }
-    *total = tot;
-    __syncthreads();  // sh may be rewritten by the next call
-    return before + incl - v;
+    return sh[0] + sh[1] + sh[2] + sh[3];
 }
 
-// One block of 1024 threads picks the digit of `pass` from histogram h
-// (nb bins; LDS or global): thread t owns bins nb-1-(t*per+j), descending,
-// and the exclusive scan gives the keys in all higher bins. Updates
-// prefix/pmask/k_rem for every thread and returns the picked bin's count.
-__device__ int64_t block_pick_1024(const uint32_t *h, int pass, uint64_t &prefix, uint64_t &pmask, int64_t &k_rem,
-                                   int64_t *s_scan, PickOut *s_out) {
-    const int t = threadIdx.x;
-    const int shift = kShift[pass];
-    const int nb = 1 << kWidth[pass];
-    const uint64_t dmask = (uint64_t)(nb - 1);
-    const int per = nb / 1024;  // 2 or 1
-    int64_t sum = 0;
-    for (int j = 0; j < per; ++j) sum += h[nb - 1 - (t * per + j)];
-    int64_t total;
-    int64_t run = block_exclusive_scan_1024(sum, s_scan, &total);
-    for (int j = 0; j < per; ++j) {
-        const int b = nb - 1 - (t * per + j);
-        const int64_t c = h[b];
-        if (run < k_rem && run + c >= k_rem) {  // exactly one (thread, bin)
-            s_out->prefix = prefix | ((uint64_t)b << shift);
-            s_out->pmask = pmask | (dmask << shift);
-            s_out->k_rem = k_rem - run;
-            s_out->count = c;
-        }
-        run += c;
-    }
-    __syncthreads();
-    prefix = s_out->prefix;
-    pmask = s_out->pmask;
-    k_rem = s_out->k_rem;
-    const int64_t count = s_out->count;
-    __syncthreads();  // every thread has read s_out before it is written again
-    return count;
-}
+// Sums of the tile counts per kCoarse tiles, for selections of more tiles
+// than the emit's blocks should add one by one.
+constexpr int kCoarse = 1024;
+constexpr int kDirectTiles = 8192;
 
-// One block of 1024 threads; thread t owns a contiguous range of tiles.
-__global__ __launch_bounds__(1024) void topk_tile_scan_kernel(int32_t nt, const TopkState *__restrict__ st,
-                                                              const uint32_t *__restrict__ tile_eq,
-                                                              const uint32_t *__restrict__ tile_gt,
-                                                              uint32_t *__restrict__ eq_before,
-                                                              uint32_t *__restrict__ sel_before) {
-    __shared__ int64_t sh[16];
-    const int t = threadIdx.x;
-    const int32_t per = (nt + 1023) / 1024;
-    const int32_t lo = min(nt, t * per), hi = min(nt, lo + per);
-    const int64_t r = st->k_rem;
-    int64_t tot;
-    int64_t s = 0;
-    for (int32_t i = lo; i < hi; ++i) s += tile_eq[i];
-    int64_t run = block_exclusive_scan_1024(s, sh, &tot);
-    int64_t sel_local = 0;
-    for (int32_t i = lo; i < hi; ++i) {
-        eq_before[i] = (uint32_t)run;
-        const int64_t take = clamp_take(r - run, tile_eq[i]);
-        sel_local += tile_gt[i] + take;
-        run += tile_eq[i];
-    }
-    int64_t srun = block_exclusive_scan_1024(sel_local, sh, &tot);
-    for (int32_t i = lo; i < hi; ++i) {
-        sel_before[i] = (uint32_t)srun;
-        const int64_t eb = eq_before[i];
-        const int64_t take = clamp_take(r - eb, tile_eq[i]);
-        srun += tile_gt[i] + take;
+__global__ __launch_bounds__(256) void topk_coarse_kernel(const uint32_t *__restrict__ tile_eq,
+                                                          const uint32_t *__restrict__ tile_gt, int32_t nt,
+                                                          uint32_t *__restrict__ coarse_eq,
+                                                          uint32_t *__restrict__ coarse_gt) {
+    __shared__ int64_t sh[2][4];
+    const int32_t lo = blockIdx.x * kCoarse, m = min(kCoarse, nt - lo);
+    const int64_t eq = block_sum_256(tile_eq + lo, m, sh[0]);
+    const int64_t gt = block_sum_256(tile_gt + lo, m, sh[1]);
+    if (threadIdx.x == 0) {
+        coarse_eq[blockIdx.x] = (uint32_t)eq;
+        coarse_gt[blockIdx.x] = (uint32_t)gt;
     }
 }
 
+// prev (nullable): receives each mask word's old value, the selection that
+// this one replaces.
+template <int kPer>
 __global__ __launch_bounds__(256) void topk_emit_kernel(const uint64_t *__restrict__ key, int32_t n,
                                                         const TopkState *__restrict__ st,
-                                                        const uint32_t *__restrict__ eq_before,
-                                                        const uint32_t *__restrict__ sel_before,
+                                                        const uint32_t *__restrict__ tile_eq,
+                                                        const uint32_t *__restrict__ tile_gt,
+                                                        const uint32_t *__restrict__ coarse_eq,
+                                                        const uint32_t *__restrict__ coarse_gt,
                                                         int32_t *__restrict__ idx,
-                                                        uint32_t *__restrict__ mask, int32_t k) {
+                                                        uint32_t *__restrict__ mask, uint32_t *__restrict__ prev,
+                                                        int32_t k) {
     __shared__ uint32_t s_eq[4], s_gt[4];
-    const uint64_t T = st->prefix;
-    const int64_t r = st->k_rem;
+    __shared__ int64_t s_sum[4][4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t lt_mask = (1ull << lane) - 1ull;
-    const int64_t wbase = (int64_t)blockIdx.x * kTile + (int64_t)w * (kTile / 4);
+    const int64_t wbase = ((int64_t)blockIdx.x * 4 + w) * (64 * kPer);
     const int64_t nwords = ((int64_t)n + 31) / 32;
+    uint64_t kv[kPer];
+#pragma unroll
+    for (int g = 0; g < kPer; ++g) kv[g] = key[std::min<int64_t>(wbase + 64 * g + lane, n - 1)];
+    const uint64_t T = st->prefix, pmask = st->pmask;
+    const int64_t r = st->k_rem;
+    // the equal and greater keys of the tiles before this one
+    int64_t eq_base, gt_base;
+    if (coarse_eq) {
+        const int32_t c = blockIdx.x / kCoarse, lo = c * kCoarse, m = blockIdx.x - lo;
+        eq_base = block_sum_256(coarse_eq, c, s_sum[0]) + block_sum_256(tile_eq + lo, m, s_sum[1]);
+        gt_base = block_sum_256(coarse_gt, c, s_sum[2]) + block_sum_256(tile_gt + lo, m, s_sum[3]);
+    } else {
+        eq_base = block_sum_256(tile_eq, blockIdx.x, s_sum[0]);
+        gt_base = block_sum_256(tile_gt, blockIdx.x, s_sum[1]);
+    }
     uint32_t eq = 0, gt = 0;
-    for (int g = 0; g < kTile / 4 / 64; ++g) {
-        const int64_t i = wbase + 64 * g + lane;
-        const bool in = i < n;
-        const uint64_t kv = in ? key[i] : 0ull;
-        eq += __popcll(__ballot(in && kv == T));
-        gt += __popcll(__ballot(in && kv > T));
+#pragma unroll
+    for (int g = 0; g < kPer; ++g) {
+        const bool in = wbase + 64 * g + lane < n;
+        kv[g] &= pmask;
+        eq += __popcll(__ballot(in && kv[g] == T));
+        gt += __popcll(__ballot(in && kv[g] > T));
     }
     if (lane == 0) { s_eq[w] = eq; s_gt[w] = gt; }
     __syncthreads();
-    int64_t eq_base = eq_before[blockIdx.x], sel_base = sel_before[blockIdx.x];
     for (int v = 0; v < w; ++v) {
-        const int64_t take = clamp_take(r - eq_base, s_eq[v]);
-        sel_base += s_gt[v] + take;
+        gt_base += s_gt[v];
         eq_base += s_eq[v];
     }
-    for (int g = 0; g < kTile / 4 / 64; ++g) {
+    // of the equal keys the first r are kept
+    int64_t sel_base = gt_base + clamp_take(r, eq_base);
+#pragma unroll
+    for (int g = 0; g < kPer; ++g) {
         const int64_t base = wbase + 64 * g;
         const int64_t i = base + lane;
         const bool in = i < n;
-        const uint64_t kv = in ? key[i] : 0ull;
-        const bool is_eq = in && kv == T;
+        const bool is_eq = in && kv[g] == T;
         const uint64_t eqbal = __ballot(is_eq);
-        const bool sel = (in && kv > T) || (is_eq && eq_base + __popcll(eqbal & lt_mask) < r);
+        const bool sel = (in && kv[g] > T) || (is_eq && eq_base + __popcll(eqbal & lt_mask) < r);
         const uint64_t selbal = __ballot(sel);
         const int64_t pos = sel_base + __popcll(selbal & lt_mask);
         if (sel && pos < k) idx[pos] = (int32_t)i;
-        const int64_t word = base / 32;
-        if (lane == 0 && word < nwords) mask[word] = (uint32_t)selbal;
-        if (lane == 32 && word + 1 < nwords) mask[word + 1] = (uint32_t)(selbal >> 32);
+        const int64_t word = base / 32 + (lane >> 5);
+        if ((lane & 31) == 0 && word < nwords) {
+            if (prev) prev[word] = mask[word];
+            mask[word] = (uint32_t)(lane == 0 ? selbal : selbal >> 32);
+        }
         eq_base += __popcll(eqbal);
         sel_base += __popcll(selbal);
     }
 }
 
-// Small inputs (n <= kSmallN) in one block of 1024 threads, the keys held in
-// LDS: the same six radix passes (LDS histogram, a block scan picks the
-// digit), then thread t takes keys [16 t, 16 t + 16): block scans of its
-// (== T) count and of its kept count give the ranks, idx is written at the
-// running kept count and each 16-bit piece of the mask is paired with its
-// neighbour's into a word. One launch instead of fifteen; same result.
+// Small inputs (n <= kSmallN) in one block of 1024 threads: thread t holds
+// keys [kPer t, kPer (t + 1)) in registers. The same radix passes (LDS
+// histogram, a block scan picks the digit) until the picked bin is wanted
+// whole, then block scans of each thread's (== T) count and of its kept count
+// give the ranks; idx is written at the running kept count and the threads of
+// 32 keys put their bits together into a mask word.
 constexpr int kSmallN = 16384;
 constexpr int kSmallThreads = 1024;
-constexpr int kSmallPer = kSmallN / kSmallThreads;  // 16 keys per thread in the emit
-static_assert(kSmallPer == 16, "two threads' 16-bit pieces make one mask word");
 
+// Exclusive scan over the block (by shuffles within each wave, then over the
+// 16 wave totals in sh). Ends with a barrier.
+__device__ __forceinline__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32_t *sh) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t incl = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t x = __shfl_up(incl, off);
+        if (lane >= off) incl += x;
+    }
+    if (lane == 63) sh[w] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+#pragma unroll
+    for (int u = 0; u < 15; ++u) before += u < w ? sh[u] : 0;
+    __syncthreads();  // sh may be rewritten by the next call
+    return before + incl - v;
+}
+
+template <int kPer>
 __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const uint64_t *__restrict__ key, int32_t n,
                                                                    int32_t k, int32_t *__restrict__ idx,
-                                                                   uint32_t *__restrict__ mask) {
-    __shared__ uint64_t s_key[kSmallN];
+                                                                   uint32_t *__restrict__ mask,
+                                                                   uint32_t *__restrict__ prev) {
     __shared__ uint32_t s_hist[kBins];
-    __shared__ int64_t s_scan[kSmallThreads / 64];
+    __shared__ uint32_t s_scan[kSmallThreads / 64];
     __shared__ PickOut s_out;
-    const int t = threadIdx.x;
-    for (int i = t; i < n; i += kSmallThreads) s_key[i] = key[i];
+    const int t = threadIdx.x, lane = t & 63;
+    const int lo = t * kPer, cnt = min(max(n - lo, 0), kPer);
+    uint64_t kv[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) kv[j] = key[min(lo + j, n - 1)];
     uint64_t prefix = 0, pmask = 0;
-    int64_t k_rem = k;
+    uint32_t k_rem = (uint32_t)k;
     for (int pass = 0; pass < kPasses; ++pass) {
-        const int shift = kShift[pass];
-        const uint64_t dmask = (1ull << kWidth[pass]) - 1ull;
+        const int shift = kShift[pass], nb = 1 << kWidth[pass];
+        const uint64_t dmask = (uint64_t)(nb - 1);
         for (int b = t; b < kBins; b += kSmallThreads) s_hist[b] = 0;
-        __syncthreads();  // keys loaded (first pass), histogram cleared
-        for (int i = t; i < n; i += kSmallThreads) {
-            const uint64_t kv = s_key[i];
-            if ((kv & pmask) == prefix) atomicAdd(&s_hist[(kv >> shift) & dmask], 1u);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const bool in = j < cnt && (kv[j] & pmask) == prefix;
+            const uint32_t dg = (uint32_t)((kv[j] >> shift) & dmask);
+            if (pass == 0) {  // the top digit is nearly constant: one atomic for a wave of one digit
+                const uint32_t d0 = __shfl(dg, 0);
+                const uint64_t same = __ballot(in && dg == d0);
+                if (lane == 0 && same) atomicAdd(&s_hist[d0], (uint32_t)__popcll(same));
+                if (in && dg != d0) atomicAdd(&s_hist[dg], 1u);
+            } else if (in) {
+                atomicAdd(&s_hist[dg], 1u);
+            }
         }
         __syncthreads();
-        block_pick_1024(s_hist, pass, prefix, pmask, k_rem, s_scan, &s_out);
-    }
-    const uint64_t T = prefix;
-    const int64_t r = k_rem;  // keys equal to T that are kept (the lowest indices)
-    const int lo = min(n, t * kSmallPer), hi = min(n, lo + kSmallPer);
-    int64_t eq = 0;
-    for (int i = lo; i < hi; ++i) eq += s_key[i] == T;
-    int64_t total;
-    int64_t eq_before = block_exclusive_scan_1024(eq, s_scan, &total);
-    uint32_t bits = 0;
-    int64_t kept = 0;
-    for (int i = lo; i < hi; ++i) {
-        const uint64_t kv = s_key[i];
-        bool sel = kv > T;
-        if (kv == T) sel = eq_before++ < r;
-        if (sel) {
-            bits |= 1u << (i - lo);
-            ++kept;
+        // thread t owns the bins nb - 1 - t per .. downwards; the scan gives the keys in higher bins
+        const int per = nb / kSmallThreads;  // 2 or 1
+        uint32_t c[2] = {s_hist[nb - 1 - t * per], per == 2 ? s_hist[nb - 2 - t * per] : 0u};
+        uint32_t run = block_exclusive_scan_1024(c[0] + c[1], s_scan);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (j < per && run < k_rem && run + c[j] >= k_rem) {  // exactly one (thread, bin)
+                const uint64_t b = (uint64_t)(nb - 1 - t * per - j);
+                s_out.prefix = prefix | (b << shift);
+                s_out.pmask = pmask | (dmask << shift);
+                s_out.k_rem = k_rem - run;
+                s_out.done = c[j] == k_rem - run;
+            }
+            run += c[j];
         }
+        __syncthreads();
+        prefix = s_out.prefix;
+        pmask = s_out.pmask;
+        k_rem = (uint32_t)s_out.k_rem;
+        if (s_out.done) break;  // block-uniform; s_out is rewritten two barriers later at the earliest
     }
-    int64_t pos = block_exclusive_scan_1024(kept, s_scan, &total);
-    for (int i = lo; i < hi; ++i)
-        if ((bits >> (i - lo)) & 1u) idx[pos++] = i;
-    const uint32_t hi16 = __shfl_down(bits, 1);  // the odd neighbour's piece
-    const int64_t word = t / 2;
-    if ((t & 1) == 0 && word < ((int64_t)n + 31) / 32) mask[word] = bits | (hi16 << 16);
+    uint32_t eq = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        kv[j] &= pmask;
+        eq += j < cnt && kv[j] == prefix;
+    }
+    uint32_t eq_before = block_exclusive_scan_1024(eq, s_scan);
+    uint32_t bits = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        bool sel = kv[j] > prefix;
+        if (kv[j] == prefix) sel = eq_before++ < k_rem;
+        if (sel && j < cnt) bits |= 1u << j;
+    }
+    uint32_t pos = block_exclusive_scan_1024(__popc(bits), s_scan);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+        if ((bits >> j) & 1u) idx[pos++] = lo + j;
+    constexpr int kLanes = 32 / kPer;  // threads per mask word
+    uint32_t word = bits << (kPer * (t % kLanes));
+#pragma unroll
+    for (int m = 1; m < kLanes; m <<= 1) word |= __shfl_xor(word, m);
+    const int at = t / kLanes;
+    if (t % kLanes == 0 && at < (n + 31) / 32) {
+        if (prev) prev[at] = mask[at];
+        mask[at] = word;
+    }
 }
 
-__global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t *p, int64_t count, uint32_t v) {
+__global__ __launch_bounds__(256) void clear_mask_kernel(uint32_t *mask, uint32_t *prev, int64_t count) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        if (prev) prev[i] = mask[i];
+        mask[i] = 0;
+    }
 }
+
+// Keys per thread of the tile kernels: small tiles until they fill the chip.
+constexpr int32_t kSmallTileN = 1 << 20;
+int tile_per(int32_t n) { return n <= kSmallTileN ? 4 : 16; }
 
 }  // namespace
 
 size_t topk_ws_bytes(int32_t n) {
-    const size_t nt = (size_t)ceil_div(std::max<int32_t>(n, 1), kTile);
-    return align_up(sizeof(TopkWs), 256) + 4 * align_up(nt * sizeof(uint32_t), 256);
+    n = std::max<int32_t>(n, 1);
+    const size_t nt = (size_t)ceil_div(n, 256 * tile_per(n)), nc = (size_t)ceil_div((int64_t)nt, kCoarse);
+    return align_up(sizeof(TopkWs), 256) + 2 * align_up(nt * sizeof(uint32_t), 256) +
+           2 * align_up(nc * sizeof(uint32_t), 256);
 }
 
 hipError_t topk_launch(const uint64_t *key, int32_t n, int32_t k, int32_t *idx, uint32_t *mask,
-                       void *ws, hipStream_t stream) {
+                       void *ws, hipStream_t stream, uint32_t *prev) {
     if (n == 0) return hipSuccess;
     const int64_t nwords = ceil_div(n, 32);
     if (k == 0) {
-        fill_u32_kernel<<<(unsigned)std::min<int64_t>(ceil_div(nwords, 256), 1024), 256, 0, stream>>>(
-            mask, nwords, 0u);
+        clear_mask_kernel<<<(unsigned)std::min<int64_t>(ceil_div(nwords, 256), 1024), 256, 0, stream>>>(mask, prev,
+                                                                                                     nwords);
         return hipGetLastError();
     }
     if (n <= kSmallN) {
-        topk_small_kernel<<<1, kSmallThreads, 0, stream>>>(key, n, k, idx, mask);
+        if (n <= 4 * kSmallThreads)
+            topk_small_kernel<4><<<1, kSmallThreads, 0, stream>>>(key, n, k, idx, mask, prev);
+        else
+            topk_small_kernel<16><<<1, kSmallThreads, 0, stream>>>(key, n, k, idx, mask, prev);
         return hipGetLastError();
     }
     TopkWs *h = static_cast<TopkWs *>(ws);
-    const int32_t nt = (int32_t)ceil_div(n, kTile);
+    const int per = tile_per(n);
+    const int32_t nt = (int32_t)ceil_div(n, 256 * per), nc = (int32_t)ceil_div(nt, kCoarse);
     char *p = static_cast<char *>(ws) + align_up(sizeof(TopkWs), 256);
-    const size_t tb = align_up((size_t)nt * sizeof(uint32_t), 256);
+    const size_t tb = align_up((size_t)nt * sizeof(uint32_t), 256), cb = align_up((size_t)nc * sizeof(uint32_t), 256);
     uint32_t *tile_eq = reinterpret_cast<uint32_t *>(p);
     uint32_t *tile_gt = reinterpret_cast<uint32_t *>(p + tb);
-    uint32_t *eq_before = reinterpret_cast<uint32_t *>(p + 2 * tb);
-    uint32_t *sel_before = reinterpret_cast<uint32_t *>(p + 3 * tb);
+    uint32_t *coarse_eq = nullptr, *coarse_gt = nullptr;
 
     topk_init_kernel<<<1, 256, 0, stream>>>(h, k);
     // Each block flushes its non-empty bins with one global atomic each. The
@@ -469,9 +515,21 @@ hipError_t topk_launch(const uint64_t *key, int32_t n, int32_t k, int32_t *idx, 
     const unsigned hgrid_pass[2] = {std::min(hgrid_wide, 256u), std::min(hgrid_wide, 128u)};
     for (int pass = 0; pass < kPasses; ++pass)
         topk_hist_kernel<<<pass < 2 ? hgrid_pass[pass] : hgrid_wide, 256, 0, stream>>>(key, n, h, pass);
-    topk_tile_count_kernel<<<nt, 256, 0, stream>>>(key, n, h, tile_eq, tile_gt);
-    topk_tile_scan_kernel<<<1, 1024, 0, stream>>>(nt, &h->st[kPasses], tile_eq, tile_gt, eq_before, sel_before);
-    topk_emit_kernel<<<nt, 256, 0, stream>>>(key, n, &h->st[kPasses], eq_before, sel_before, idx, mask, k);
+    if (per == 4)
+        topk_tile_count_kernel<4><<<nt, 256, 0, stream>>>(key, n, h, tile_eq, tile_gt);
+    else
+        topk_tile_count_kernel<16><<<nt, 256, 0, stream>>>(key, n, h, tile_eq, tile_gt);
+    if (nt > kDirectTiles) {
+        coarse_eq = reinterpret_cast<uint32_t *>(p + 2 * tb);
+        coarse_gt = reinterpret_cast<uint32_t *>(p + 2 * tb + cb);
+        topk_coarse_kernel<<<nc, 256, 0, stream>>>(tile_eq, tile_gt, nt, coarse_eq, coarse_gt);
+    }
+    if (per == 4)
+        topk_emit_kernel<4><<<nt, 256, 0, stream>>>(key, n, &h->st[kPasses], tile_eq, tile_gt, coarse_eq, coarse_gt,
+                                                    idx, mask, prev, k);
+    else
+        topk_emit_kernel<16><<<nt, 256, 0, stream>>>(key, n, &h->st[kPasses], tile_eq, tile_gt, coarse_eq, coarse_gt,
+                                                     idx, mask, prev, k);
     return hipGetLastError();
 }
 
