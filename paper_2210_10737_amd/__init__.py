@@ -206,22 +206,20 @@ def _ptr(t: torch.Tensor | None) -> int | None:
     return None if t is None else _dp(t)
 
 
-def _ld(t: torch.Tensor) -> int:
-    if t.dim() != 2 or t.stride(1) != 1:
-        raise ValueError("dense operands must be 2-D with unit column stride")
-    return t.stride(0)
-
-
 def _dense(t: torch.Tensor, rows: int, d: int, name: str) -> tuple[int, int]:
     """(device address, leading dimension) of a float32 operand that holds at
     least rows x d elements: the library reads or writes that many through
-    the pointer, so a smaller or differently typed tensor is refused here."""
+    the pointer, so a smaller or differently typed tensor is refused here.
+    (Small products are bound by host time per call, so each property is read
+    from the tensor once.)"""
     if t.dtype != torch.float32:
         raise ValueError(f"{name}: dtype {t.dtype}, float32 expected")
-    ld = _ld(t)
-    if t.shape[0] < rows or t.shape[1] < d:
-        raise ValueError(f"{name}: shape {tuple(t.shape)} holds less than {rows} x {d}")
-    return _dp(t), ld
+    shape, stride = t.shape, t.stride()
+    if len(shape) != 2 or stride[1] != 1:
+        raise ValueError("dense operands must be 2-D with unit column stride")
+    if shape[0] < rows or shape[1] < d:
+        raise ValueError(f"{name}: shape {tuple(shape)} holds less than {rows} x {d}")
+    return _dp(t), stride[0]
 
 
 def _vec_check(t: torch.Tensor, count: int, dtype, name: str) -> None:
@@ -241,7 +239,8 @@ def _vec(t: torch.Tensor | None, count: int, dtype, name: str) -> int | None:
 def _new_out(rows: int, d: int, device) -> torch.Tensor:
     """rows x d output view with a leading dimension rounded up to 4 floats."""
     ld = (d + 3) // 4 * 4
-    return torch.empty((rows, ld), dtype=torch.float32, device=device)[:, :d]
+    out = torch.empty((rows, ld), dtype=torch.float32, device=device)
+    return out if ld == d else out[:, :d]
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
@@ -275,10 +274,8 @@ class DeviceCsr:
         if self.nnz:
             _vec_check(self.col, self.nnz, torch.int32, "col")
             _vec_check(self.val, self.nnz, torch.float32, "val")
-        return CsrStruct(self.n_rows, self.n_cols, self.nnz,
-                         _vec(self.rowptr, self.n_rows + 1, torch.int32, "rowptr"),
-                         _vec(self.col, self.nnz, torch.int32, "col") if self.nnz else None,
-                         _vec(self.val, self.nnz, torch.float32, "val") if self.nnz else None)
+        return CsrStruct(self.n_rows, self.n_cols, self.nnz, _dp(self.rowptr),
+                         _dp(self.col) if self.nnz else None, _dp(self.val) if self.nnz else None)
 
 
 # ---------------------------------------------------------------- A1

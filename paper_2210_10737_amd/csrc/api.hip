@@ -152,25 +152,38 @@ rsc_status_t check_same_device(int made_on, const char *what) {
 }
 
 // Completion markers of the work a plan or cache has enqueued: one event per
-// stream it was used on, recorded after each call (not while the stream is
-// being captured into a graph: a captured call runs when the caller launches
-// the graph, which the caller synchronises). Destroying the handle waits for
-// these events only, so work on other streams is never waited for.
+// stream it was used on, recorded behind each call's last launch (not while
+// the stream is being captured into a graph: a captured call runs when the
+// caller launches the graph, which the caller synchronises). Destroying the
+// handle waits for these events only, so work on other streams is never
+// waited for.
 struct StreamFence {
     std::vector<std::pair<hipStream_t, hipEvent_t>> ev;
 
-    hipError_t record(hipStream_t s) {
+    // The event to record on s behind the call's work; NULL under capture.
+    hipError_t event_for(hipStream_t s, hipEvent_t *out) {
+        *out = nullptr;
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         hipError_t e = hipStreamIsCapturing(s, &cs);
         if (e != hipSuccess) return e;
         if (cs != hipStreamCaptureStatusNone) return hipSuccess;
         for (auto &p : ev)
-            if (p.first == s) return hipEventRecord(p.second, s);
+            if (p.first == s) {
+                *out = p.second;
+                return hipSuccess;
+            }
         hipEvent_t x = nullptr;
         e = hipEventCreateWithFlags(&x, hipEventDisableTiming);
         if (e != hipSuccess) return e;
         ev.emplace_back(s, x);
-        return hipEventRecord(x, s);
+        *out = x;
+        return hipSuccess;
+    }
+
+    hipError_t record(hipStream_t s) {
+        hipEvent_t x = nullptr;
+        const hipError_t e = event_for(s, &x);
+        return e == hipSuccess && x ? hipEventRecord(x, s) : e;
     }
 
     // waits for every recorded event and releases them; the first error
@@ -274,7 +287,8 @@ struct rsc_cache {
     int64_t *h_nnz = nullptr;  // pinned
     void *ws_topk = nullptr, *ws_slice = nullptr, *ws_spmm = nullptr;
     size_t ws_topk_bytes = 0, ws_slice_bytes = 0, ws_spmm_bytes = 0;
-    hipEvent_t ev = nullptr;
+    hipEvent_t ev = nullptr;   // behind the latest slice
+    bool ev_recorded = false;  // outside a capture
     int32_t *s_split = nullptr;  // the slice's column-blocked split bounds (when its product is blocked)
     int32_t split_P = 0;          // ranges s_split has room for
     rsc::SpmmPrepared prep;       // the slice product's row list, prepared at each refresh (in ws_spmm)
@@ -477,15 +491,16 @@ rsc_status_t rsc_spmm_plan_run(rsc_spmm_plan_t *p, const float *B, int32_t d, in
     RSC_TRY(check_dense(Y, A->n_rows, d, ldy, "Y"));
     RSC_TRY(check_same_device(p->device, "plan"));
     bool used = false;
+    hipEvent_t stop = nullptr;
+    RSC_HIP(p->fence.event_for(stream, &stop), "plan run event");
     const hipError_t e = rsc::spmm_launch(A->n_rows, A->n_cols, A->nnz, A->rowptr, p->colf ? p->colf : A->col,
                                           A->val, B, d, ldb, Y, ldy, p->ws, p->ws_bytes, stream, A->nnz, A->n_cols,
-                                          p->colf != nullptr, &p->prep, &used);
+                                          p->colf != nullptr, &p->prep, &used, stop);
     // a run whose decisions differed (an environment switch changed since the
     // plan was made) rebuilt its own row list in the plan's workspace: from
     // then on every run prepares for itself
     if (!used && A->n_rows > 0) p->prep.ready = false;
     RSC_HIP(e, "plan run");
-    RSC_HIP(p->fence.record(stream), "plan run event");
     return RSC_OK;
 }
 
@@ -786,7 +801,8 @@ static uint32_t *previous_selection(rsc_cache_t *c) {
 // last scored operand's) would build first (split bounds when blocked, else
 // the row order where it is used), built once. Asynchronous (the number of
 // long rows stays on the device).
-static hipError_t cache_prepare(rsc_cache_t *c, int32_t d, hipStream_t stream) {
+static hipError_t cache_prepare(rsc_cache_t *c, int32_t d, hipStream_t stream, bool *launched) {
+    *launched = false;
     c->prep = rsc::SpmmPrepared{};
     const rsc_csr_t &X = c->X;
     if (X.n_rows == 0) return hipSuccess;
@@ -803,6 +819,7 @@ static hipError_t cache_prepare(rsc_cache_t *c, int32_t d, hipStream_t stream) {
         c->prep.list = c->prep.ordered || (c->x_long_rows != 0 && rsc::spmm_lists_long_rows(X.n_rows));
         e = c->prep.list ? rsc::spmm_rows_prepare(X.n_rows, X.nnz, c->s_rowptr, c->ws_spmm, stream) : hipSuccess;
     }
+    *launched = P > 1 || c->prep.list;
     c->prep.P = P;
     c->prep.long_rows = c->x_long_rows == 0 ? 0 : -1;  // else the length stays on the device
     c->prep.ready = e == hipSuccess;
@@ -813,11 +830,22 @@ rsc_status_t rsc_cache_score(rsc_cache_t *c, const float *B, int32_t d, int64_t 
     if (!c) return fail(RSC_ERR_INVALID_ARGUMENT, "cache is NULL");
     RSC_TRY(check_dense(B, c->n, d, ldb, "B"));
     RSC_TRY(check_same_device(c->device, "cache"));
+    hipEvent_t stop = nullptr;
+    RSC_HIP(c->fence.event_for(stream, &stop), "cache event");
     RSC_HIP(rsc::pair_scores_launch(c->cn2, B, c->n, d, ldb, c->key, nullptr, c->rn2, stream), "cache scores");
-    RSC_HIP(rsc::sum_fixed_order_launch(c->rn2, c->n, c->sum_ws, c->norms + 1, stream), "cache norm sum");
+    RSC_HIP(rsc::sum_fixed_order_launch(c->rn2, c->n, c->sum_ws, c->norms + 1, stream, stop), "cache norm sum");
     c->scored = true;
     c->score_d = d;
-    RSC_HIP(c->fence.record(stream), "cache event");
+    return RSC_OK;
+}
+
+// After the slice's launches: c->ev is recorded behind them (by the last one,
+// or here under capture).
+static rsc_status_t slice_enqueued(rsc_cache_t *c, hipEvent_t stop, hipStream_t stream) {
+    if (stop)
+        c->ev_recorded = true;
+    else
+        RSC_HIP(hipEventRecord(c->ev, stream), "cache event");
     return RSC_OK;
 }
 
@@ -826,18 +854,22 @@ rsc_status_t rsc_cache_select(rsc_cache_t *c, int32_t k, int64_t step, hipStream
     if (k < 0 || k > c->n) return fail(RSC_ERR_INVALID_ARGUMENT, "k = %d outside [0, %d]", k, c->n);
     if (!c->scored) return fail(RSC_ERR_INVALID_ARGUMENT, "cache select before any score");
     RSC_TRY(check_same_device(c->device, "cache"));
+    hipEvent_t stop = nullptr;  // NULL under capture
+    RSC_HIP(c->fence.event_for(stream, &stop), "cache event");
     RSC_HIP(rsc::topk_launch(c->key, c->n, k, c->idx, c->mask, c->ws_topk, stream, previous_selection(c)), "cache topk");
     RSC_HIP(rsc::slice_launch(c->X.n_rows, c->X.n_cols, c->X.nnz, c->X.rowptr, c->X.col, c->X.val, c->mask, c->s_rowptr,
-                              c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, nullptr, c->h_nnz),
+                              c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, nullptr, c->h_nnz,
+                              stop ? c->ev : nullptr),
             "cache slice");
-    RSC_HIP(hipEventRecord(c->ev, stream), "cache event");
+    RSC_TRY(slice_enqueued(c, stop, stream));
     c->k = k;
     c->last_step = step;
     c->version += 1;
     c->nnz_known = false;
     c->random = false;
-    RSC_HIP(cache_prepare(c, c->score_d, stream), "cache slice preparation");
-    RSC_HIP(c->fence.record(stream), "cache event");
+    bool launched = false;
+    RSC_HIP(cache_prepare(c, c->score_d, stream, &launched), "cache slice preparation");
+    if (launched) RSC_HIP(c->fence.record(stream), "cache event");  // else c->ev stands behind the last launch
     return RSC_OK;
 }
 
@@ -848,20 +880,24 @@ rsc_status_t rsc_cache_refresh_random(rsc_cache_t *c, const float *B, int32_t d,
     if (k_draws < 0) return fail(RSC_ERR_INVALID_ARGUMENT, "k_draws < 0");
     RSC_TRY(check_same_device(c->device, "cache"));
     RSC_TRY(rsc_cache_score(c, B, d, ldb, stream));
+    hipEvent_t stop = nullptr;  // NULL under capture
+    RSC_HIP(c->fence.event_for(stream, &stop), "cache event");
     RSC_HIP(rsc::sample_launch(c->key, c->n, k_draws, seed, c->count, c->colw, c->mask, c->ws_sample, stream,
                                previous_selection(c)),
             "cache sample");
     RSC_HIP(rsc::slice_launch(c->X.n_rows, c->X.n_cols, c->X.nnz, c->X.rowptr, c->X.col, c->X.val, c->mask, c->s_rowptr,
-                              c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, c->colw, c->h_nnz),
+                              c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, c->colw, c->h_nnz,
+                              stop ? c->ev : nullptr),
             "cache weighted slice");
-    RSC_HIP(hipEventRecord(c->ev, stream), "cache event");
+    RSC_TRY(slice_enqueued(c, stop, stream));
     c->k = k_draws;
     c->last_step = step;
     c->version += 1;
     c->nnz_known = false;
     c->random = true;
-    RSC_HIP(cache_prepare(c, c->score_d, stream), "cache slice preparation");
-    RSC_HIP(c->fence.record(stream), "cache event");
+    bool launched = false;
+    RSC_HIP(cache_prepare(c, c->score_d, stream, &launched), "cache slice preparation");
+    if (launched) RSC_HIP(c->fence.record(stream), "cache event");  // else c->ev stands behind the last launch
     return RSC_OK;
 }
 
@@ -916,12 +952,13 @@ rsc_status_t rsc_spmm_sampled(rsc_cache_t *c, const float *B, int32_t d, int64_t
     const int64_t kk = std::min<int64_t>(c->k, c->n);
     const int64_t nnz_hint = c->n > 0 ? c->X.nnz * kk / c->n : 0;
     bool used = false;
+    hipEvent_t stop = nullptr;
+    RSC_HIP(c->fence.event_for(stream, &stop), "cache event");
     const hipError_t e = rsc::spmm_launch(c->X.n_rows, c->X.n_cols, c->X.nnz, c->s_rowptr, c->s_col, c->s_val, B, d,
                                           ldb, Y, ldy, c->ws_spmm, c->ws_spmm_bytes, stream, nnz_hint, kk, false,
-                                          &c->prep, &used);
+                                          &c->prep, &used, stop);
     if (!used) c->prep.ready = false;  // the launch rebuilt its own list in ws_spmm
     RSC_HIP(e, "spmm_sampled launch");
-    RSC_HIP(c->fence.record(stream), "cache event");
     return RSC_OK;
 }
 
@@ -1004,7 +1041,11 @@ rsc_status_t rsc_cache_staleness(rsc_cache_t *c, const int32_t *order, double *a
 
 rsc_status_t rsc_cache_destroy(rsc_cache_t *c) {
     if (!c) return RSC_OK;
-    const hipError_t e = c->fence.wait_and_release();  // the cache's own work only
+    hipError_t e = c->fence.wait_and_release();  // the cache's own work only
+    if (c->ev_recorded) {
+        const hipError_t ee = hipEventSynchronize(c->ev);
+        if (e == hipSuccess) e = ee;
+    }
     cache_free(c, c->free_stream);
     if (e != hipSuccess) return hip_fail(e, "cache destroy");
     return RSC_OK;

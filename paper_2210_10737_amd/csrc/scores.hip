@@ -256,14 +256,15 @@ __global__ __launch_bounds__(kSumThreads) void sum_parts_kernel(const double *__
 
 size_t sum_ws_bytes(int64_t n) { return sizeof(double) * (size_t)std::max<int64_t>(1, ceil_div(n, kSumChunk)); }
 
-hipError_t sum_fixed_order_launch(const double *x, int64_t n, double *ws, double *out, hipStream_t stream) {
+hipError_t sum_fixed_order_launch(const double *x, int64_t n, double *ws, double *out, hipStream_t stream,
+                                  hipEvent_t stop) {
     const int64_t np = ceil_div(n, kSumChunk);
     if (np == 1) {  // one block's sum is the total (adding it to zeros changes nothing)
-        sum_chunks_kernel<<<1, kSumThreads, 0, stream>>>(x, n, out);
+        launch(sum_chunks_kernel, 1, kSumThreads, stream, stop, x, n, out);
         return hipGetLastError();
     }
     if (np > 0) sum_chunks_kernel<<<(unsigned)np, kSumThreads, 0, stream>>>(x, n, ws);
-    sum_parts_kernel<<<1, kSumThreads, 0, stream>>>(ws, np, out);
+    launch(sum_parts_kernel, 1, kSumThreads, stream, stop, (const double *)ws, np, out);
     return hipGetLastError();
 }
 

@@ -587,11 +587,13 @@ size_t slice_ws_bytes(int64_t nnz) {
 hipError_t slice_launch(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *col,
                         const float *val, const uint32_t *mask, int32_t *rowptr_out,
                         int32_t *col_out, float *val_out, int64_t capacity, int64_t *nnz_out,
-                        void *ws, hipStream_t stream, const double *colw, int64_t *nnz_host) {
+                        void *ws, hipStream_t stream, const double *colw, int64_t *nnz_host,
+                        hipEvent_t stop) {
     if (nnz == 0) {
         zero_rows_kernel<<<(unsigned)std::min<int64_t>(ceil_div((int64_t)n_rows + 1, 256), 1024), 256, 0,
                            stream>>>(rowptr_out, (int64_t)n_rows + 1, nnz_out, nnz_host);
-        return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess && stop ? hipEventRecord(stop, stream) : e;
     }
     const int32_t nt = (int32_t)ceil_div(nnz, kTile);
     const size_t tb = align_up((size_t)nt * sizeof(uint32_t), 256);
@@ -626,39 +628,39 @@ hipError_t slice_launch(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32
             slice_fused_kernel<false, kFusedSub><<<grid, kFusedThreads, 0, stream>>>(
                 rowptr, n_rows, col, val, nnz, mask, n_words, nt2, status, ticket, rowptr_out, col_out, val_out,
                 capacity, nnz_out, ticket + 1, colw);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess || !nnz_host) return e;
-        return hipMemcpyAsync(nnz_host, nnz_out, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess && nnz_host)
+            e = hipMemcpyAsync(nnz_host, nnz_out, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
+        return e == hipSuccess && stop ? hipEventRecord(stop, stream) : e;
     }
     const bool small = n_words > 0 && n_words <= kSmallWords && nt <= kSmallTiles;
-    if (small) {
-        slice_count_small_kernel<<<nt, 256, 0, stream>>>(rowptr, n_rows, col, nnz, mask, n_words, nt, tile_row,
-                                                         tile_cnt, tile_bits);
-        slice_emit_kernel<<<nt, 256, 0, stream>>>(rowptr, n_rows, col, val, nnz, tile_bits, tile_cnt, nullptr,
-                                                  tile_row, rowptr_out, col_out, val_out, capacity, nnz_out, nnz_host,
-                                                  colw);
-        return hipGetLastError();
-    }
     // a mask of two LDS pieces is tested by pairs of blocks (one piece each,
     // the same tiles at the same time), given whole groups of 16 blocks
     const int32_t n_pieces = (int32_t)ceil_div(std::max<int32_t>(n_words, 1), kMaskLdsWords);
     const int64_t pair_grid = std::min<int64_t>(cus, 2 * ceil_div(nt, kTilesPerIterPaired)) / 16 * 16;
     const bool paired = n_pieces == 2 && pair_grid >= 16 && paired_count();
-    slice_tile_rows_kernel<<<(unsigned)std::min<int64_t>(ceil_div(std::max<int64_t>((int64_t)n_rows + 1, nt), 256),
-                                                         4096),
-                             256, 0, stream>>>(rowptr, n_rows, nt, tile_row, tile_cnt, paired ? tile_bits : nullptr);
-    if (paired) {
-        slice_count_kernel<true, kTilesPerIterPaired><<<(unsigned)pair_grid, kCountThreads, 0, stream>>>(
-            col, nnz, mask, n_words, nt, tile_cnt, tile_bits);
+    if (small) {
+        slice_count_small_kernel<<<nt, 256, 0, stream>>>(rowptr, n_rows, col, nnz, mask, n_words, nt, tile_row,
+                                                         tile_cnt, tile_bits);
+        coarse_cnt = nullptr;
     } else {
-        const unsigned cgrid =
-            (unsigned)std::max<int64_t>(1, std::min<int64_t>(cus, ceil_div(nt, kTilesPerIterSingle)));
-        slice_count_kernel<false, kTilesPerIterSingle><<<cgrid, kCountThreads, 0, stream>>>(
-            col, nnz, mask, n_words, nt, tile_cnt, tile_bits);
+        slice_tile_rows_kernel<<<(unsigned)std::min<int64_t>(ceil_div(std::max<int64_t>((int64_t)n_rows + 1, nt), 256),
+                                                             4096),
+                                 256, 0, stream>>>(rowptr, n_rows, nt, tile_row, tile_cnt, paired ? tile_bits : nullptr);
+        if (paired) {
+            slice_count_kernel<true, kTilesPerIterPaired><<<(unsigned)pair_grid, kCountThreads, 0, stream>>>(
+                col, nnz, mask, n_words, nt, tile_cnt, tile_bits);
+        } else {
+            const unsigned cgrid =
+                (unsigned)std::max<int64_t>(1, std::min<int64_t>(cus, ceil_div(nt, kTilesPerIterSingle)));
+            slice_count_kernel<false, kTilesPerIterSingle><<<cgrid, kCountThreads, 0, stream>>>(
+                col, nnz, mask, n_words, nt, tile_cnt, tile_bits);
+        }
+        slice_coarse_kernel<<<(unsigned)ceil_div(nt, kCoarse), kCoarse, 0, stream>>>(tile_cnt, nt, coarse_cnt);
     }
-    slice_coarse_kernel<<<(unsigned)ceil_div(nt, kCoarse), kCoarse, 0, stream>>>(tile_cnt, nt, coarse_cnt);
-    slice_emit_kernel<<<nt, 256, 0, stream>>>(rowptr, n_rows, col, val, nnz, tile_bits, tile_cnt, coarse_cnt, tile_row,
-                                              rowptr_out, col_out, val_out, capacity, nnz_out, nnz_host, colw);
+    launch(slice_emit_kernel, (unsigned)nt, 256, stream, stop, rowptr, n_rows, col, val, nnz,
+           (const uint64_t *)tile_bits, (const uint32_t *)tile_cnt, (const uint32_t *)coarse_cnt,
+           (const int32_t *)tile_row, rowptr_out, col_out, val_out, capacity, nnz_out, nnz_host, colw);
     return hipGetLastError();
 }
 

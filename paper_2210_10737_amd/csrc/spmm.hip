@@ -923,7 +923,8 @@ struct LongRows {
 hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const int32_t *rowptr,
                        const int32_t *col, const float *val, const float *B, int32_t d, int64_t ldb, float *Y,
                        int64_t ldy, void *ws, size_t ws_bytes, hipStream_t stream, int64_t nnz_hint,
-                       int64_t n_src_hint, bool hint_cols, const SpmmPrepared *prep, bool *used_prep) {
+                       int64_t n_src_hint, bool hint_cols, const SpmmPrepared *prep, bool *used_prep,
+                       hipEvent_t stop) {
     if (used_prep) *used_prep = false;
     if (n_rows == 0) return hipSuccess;
     SpmmWs *h = static_cast<SpmmWs *>(ws);
@@ -981,8 +982,8 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
 #undef RSC_SPMM_BLOCKED_LAUNCH_B
 #undef RSC_SPMM_BLOCKED_LAUNCH
             const int64_t nc = (int64_t)n_rows * ((dl + 3) / 4);
-            combine_blocks_kernel<<<(unsigned)ceil_div(nc, 256), 256, 0, stream>>>(part, W, n_rows, P, dl,
-                                                                                  Y + f0, ldy);
+            launch(combine_blocks_kernel, (unsigned)ceil_div(nc, 256), 256, stream, f0 + W >= d ? stop : nullptr,
+                   (const float *)part, (int64_t)W, n_rows, P, dl, Y + f0, ldy);
         }
         return hipGetLastError();
     }
@@ -1015,10 +1016,10 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
         const int32_t dl = std::min<int32_t>(d - f0, slice);
         const uint32_t bb = buffer_bytes(n_cols, ldb, dl);
 #define RSC_SPMM_LAUNCH_W(LPE_, NV_, H_, BUF_, COOP_, W_)                                              \
-    spmm_kernel<LPE_, NV_, true, H_, BUF_, COOP_, W_>                                                  \
-        <<<(unsigned)(lr.n_long + ceil_div(n_rows, W_)), W_ * 64, 0, stream>>>(                        \
-            rowptr, 1, col, val, B + f0, ldb, bb, Y + f0, ldy, n_rows, dl, lr.n_long, list,            \
-            ordered ? 1 : 0, &h->long_count)
+    launch(spmm_kernel<LPE_, NV_, true, H_, BUF_, COOP_, W_>,                                          \
+           (unsigned)(lr.n_long + ceil_div(n_rows, W_)), W_ * 64, stream, f0 + dl >= d ? stop : nullptr, \
+           rowptr, (int64_t)1, col, val, B + f0, ldb, bb, Y + f0, ldy, n_rows, dl, lr.n_long,          \
+           (const int32_t *)list, (int32_t)(ordered ? 1 : 0), (const int32_t *)&h->long_count)
 #define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_, BUF_, W_)                  \
     do {                                                            \
         if (lr.coop)                                                \
