@@ -113,3 +113,20 @@ def test_previous_selection_is_kept():
                 _, both, prev_k = cache.staleness(order)
                 assert prev_k == masks[-2].sum() and both == (masks[-2] & masks[-1]).sum(), (n, step)
         cache.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 257, 1023, 1024, 1025, 65_537, 1024 * 8192, 1024 * 8192 + 1])
+def test_sampler_tile_edges(n):
+    """The sampler's CDF around its tiles of 1,024 columns, around the 256
+    block maxima, and on both sides of 8,192 tiles, from which on the tile
+    sums are scanned by a launch of their own: whole numbers, the oracle's."""
+    rng = np.random.default_rng(n)
+    key = (rng.random(n) ** 3 + 1e-12).view(np.uint64) + np.uint64(1)
+    key[rng.random(n) < 0.2] = 0
+    key[n - 1] = np.uint64(0x4010000000000001)  # the largest one last
+    k = min(n, 50_000) + 3
+    o = oracle.sample_columns(key, k, n)
+    count, colw, mask = rsc.sample_columns(torch.from_numpy(key.view(np.int64)).cuda(), k, n)
+    assert np.array_equal(count.cpu().numpy(), o["count"])
+    assert np.array_equal(colw.cpu().numpy().view(np.uint64), o["colw"].view(np.uint64))
+    assert np.array_equal(mask.cpu().numpy().view(np.uint32), o["mask"])
