@@ -885,7 +885,7 @@ def main() -> int:
             frac_of_gather_output_ceiling=round(probe_sampled_out["ms"] / float(np.median(per["sampled"])), 4)),
         "roofline": {
             "bound": "hbm",
-            "kernel": "spmm_long_kernel + spmm_rows_kernel (the exact SpMM, one plan run)",
+            "kernel": "spmm_kernel (the exact SpMM, one plan run)",
             "achieved": round(achieved, 2),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

@@ -940,8 +940,7 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
         char *p = static_cast<char *>(ws) + head;
         float *part = reinterpret_cast<float *>(p + align_up(sizeof(int32_t) * (size_t)n_rows * (P + 1), 256));
         const int32_t nv = P * n_rows;  // virtual rows, block-major
-        // split bounds and the long-piece list: a plan's, prepared once (the
-        // list then already sits in this workspace), or this call's
+        // split bounds: a plan's, prepared once, or this call's
         const bool pre = prep && prep->ready && prep->P == P && prep->split;
         if (used_prep) *used_prep = pre;
         const int32_t *S = pre ? prep->split : reinterpret_cast<const int32_t *>(p);
