@@ -326,7 +326,8 @@ rsc_status_t rsc_sample_columns(const uint64_t *key, int32_t n, int32_t k, uint6
  *     the slice with each kept column scaled by its colw; rsc_cache_get then
  *     reports k = k_draws and no index list (idx_out = NULL).
  *   rsc_cache_get (host only): returns the current slice (its nnz is read
- *     from the device once per refresh, waiting for the refresh if needed),
+ *     from the device once per refresh, waiting for the refresh if needed;
+ *     one captured into a HIP graph is not waited for: synchronise its launch),
  *     the ascending kept indices, k, the slice version (0 = never
  *     refreshed, +1 per refresh) and needs_refresh = (never refreshed) or
  *     (step - last_refresh_step >= refresh_interval). The returned pointers

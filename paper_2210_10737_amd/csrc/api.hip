@@ -287,8 +287,9 @@ struct rsc_cache {
     int64_t *h_nnz = nullptr;  // pinned
     void *ws_topk = nullptr, *ws_slice = nullptr, *ws_spmm = nullptr;
     size_t ws_topk_bytes = 0, ws_slice_bytes = 0, ws_spmm_bytes = 0;
-    hipEvent_t ev = nullptr;   // behind the latest slice
-    bool ev_recorded = false;  // outside a capture
+    hipEvent_t ev = nullptr;     // behind the latest slice made outside a capture
+    bool ev_recorded = false;
+    bool slice_captured = false; // the latest slice runs when the caller launches its graph
     int32_t *s_split = nullptr;  // the slice's column-blocked split bounds (when its product is blocked)
     int32_t split_P = 0;          // ranges s_split has room for
     rsc::SpmmPrepared prep;       // the slice product's row list, prepared at each refresh (in ws_spmm)
@@ -839,14 +840,12 @@ rsc_status_t rsc_cache_score(rsc_cache_t *c, const float *B, int32_t d, int64_t 
     return RSC_OK;
 }
 
-// After the slice's launches: c->ev is recorded behind them (by the last one,
-// or here under capture).
-static rsc_status_t slice_enqueued(rsc_cache_t *c, hipEvent_t stop, hipStream_t stream) {
-    if (stop)
-        c->ev_recorded = true;
-    else
-        RSC_HIP(hipEventRecord(c->ev, stream), "cache event");
-    return RSC_OK;
+// After the slice's launches, whose last one recorded c->ev unless they were
+// captured: an event last recorded in a capture cannot be waited for, so
+// nothing is recorded there.
+static void slice_enqueued(rsc_cache_t *c, hipEvent_t stop) {
+    c->slice_captured = !stop;
+    if (stop) c->ev_recorded = true;
 }
 
 rsc_status_t rsc_cache_select(rsc_cache_t *c, int32_t k, int64_t step, hipStream_t stream) {
@@ -861,7 +860,7 @@ rsc_status_t rsc_cache_select(rsc_cache_t *c, int32_t k, int64_t step, hipStream
                               c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, nullptr, c->h_nnz,
                               stop ? c->ev : nullptr),
             "cache slice");
-    RSC_TRY(slice_enqueued(c, stop, stream));
+    slice_enqueued(c, stop);
     c->k = k;
     c->last_step = step;
     c->version += 1;
@@ -889,7 +888,7 @@ rsc_status_t rsc_cache_refresh_random(rsc_cache_t *c, const float *B, int32_t d,
                               c->s_col, c->s_val, c->X.nnz, c->d_nnz, c->ws_slice, stream, c->colw, c->h_nnz,
                               stop ? c->ev : nullptr),
             "cache weighted slice");
-    RSC_TRY(slice_enqueued(c, stop, stream));
+    slice_enqueued(c, stop);
     c->k = k_draws;
     c->last_step = step;
     c->version += 1;
@@ -923,7 +922,7 @@ rsc_status_t rsc_cache_get(rsc_cache_t *c, int64_t step, rsc_csr_t *slice_out, c
         s.n_cols = c->X.n_cols;
         if (c->version) {
             if (!c->nnz_known) {
-                RSC_HIP(hipEventSynchronize(c->ev), "cache get wait");
+                if (!c->slice_captured) RSC_HIP(hipEventSynchronize(c->ev), "cache get wait");
                 if (*c->h_nnz < 0) return fail(RSC_ERR_INTERNAL, "cache slice: the single-pass scan did not complete");
                 c->nnz_slice = *c->h_nnz;
                 c->nnz_known = true;

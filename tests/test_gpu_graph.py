@@ -120,3 +120,36 @@ def test_graph_replays_plan_run():
         assert torch.equal(Y, want), f"replay {r}"
     del g
     plan.close()
+
+
+@pytest.mark.parametrize("n", [3000, 20_000])
+@pytest.mark.parametrize("order", ["eager_captured", "captured_eager"])
+def test_captured_refresh_then_destroy(n, order):
+    """A refresh captured after (or before) an eager one: each replay selects
+    and slices like an eager refresh, and destroying the cache afterwards
+    waits for its eager work only, with no event of the capture."""
+    A = synth.erdos_renyi(n, 8.0 / n, seed=n)
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n)
+    Gm = torch.from_numpy(synth.dense_normal(n, 64, seed=n + 1)).cuda()
+    cache, ref = rsc.Cache(X, X), rsc.Cache(X, X)
+    k = n // 3
+    if order == "eager_captured":
+        cache.refresh(Gm, k // 2, step=0)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        cache.refresh(Gm, k, step=1)
+    for r in range(3):
+        Gm.copy_(torch.from_numpy(synth.dense_normal(n, 64, seed=n + 10 + r)).cuda())
+        g.replay()
+        torch.cuda.synchronize()
+        ref.refresh(Gm, k, step=r)
+        assert torch.equal(cache.spmm_sampled(Gm), ref.spmm_sampled(Gm)), r
+    assert cache.get(1)["slice"].nnz == ref.get(1)["slice"].nnz
+    if order == "captured_eager":
+        cache.refresh(Gm, k // 2, step=2)
+        ref.refresh(Gm, k // 2, step=4)
+        assert cache.get(2)["slice"].nnz == ref.get(4)["slice"].nnz
+    del g
+    cache.close()   # raises what destroy returns
+    ref.close()
