@@ -111,7 +111,9 @@ rsc_status_t rsc_csr_validate(const rsc_csr_t *A, int64_t *bad_row_host, hipStre
  * rows spans 2..16 ranges of about 4.5 MiB and rows hold at least 56, 112 or
  * 224 entries per range on average (64-, 32-, 16-float passes), the columns
  * are cut into P = min(8, ranges) equal index ranges (64-float passes: of
- * about 3 MiB, up to 12, while a row keeps 56 entries per range) processed one after
+ * about 3 MiB, up to 12, while a row keeps 56 entries per range and, where
+ * rsc_spmm_noalloc's scratch holds the buffers of the wider ranges, while it
+ * holds those of the finer ones) processed one after
  * another (the gathered B rows then stay in L2, or mostly so for ranges of
  * up to two L2 sizes); each row's entries in one range are summed as above and rounded
  * to an fp32 partial, and the P partials are added in fp64 in range order

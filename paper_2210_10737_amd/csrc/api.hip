@@ -356,7 +356,7 @@ rsc_status_t rsc_spmm(const rsc_csr_t *A, const float *B, int32_t d, int64_t ldb
 // stand-in in host code; the device address of the current GPU's copy comes
 // from hipGetSymbolAddress (looked up once per device, with that device
 // current) and only that address is passed to kernels.
-constexpr size_t kNoallocScratchBytes = size_t(32) << 20;
+using rsc::kNoallocScratchBytes;
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
 
 namespace {

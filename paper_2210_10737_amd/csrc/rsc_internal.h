@@ -68,6 +68,8 @@ bool spmm_hint_taken(int64_t n_src, int32_t d, int32_t slice);
 hipError_t spmm_rows_prepare(int32_t n_rows, int64_t nnz_bound, const int32_t *rowptr, void *ws,
                              hipStream_t stream);
 size_t spmm_blocked_fits(int32_t n_rows, int32_t P);  // workspace bytes the blocked mode needs
+// rsc_spmm_noalloc's scratch
+constexpr size_t kNoallocScratchBytes = size_t(32) << 20;
 // workspace bytes an unblocked product needs (header and row list); with at
 // least this much a launch runs, blocked only if the blocked buffers also fit
 size_t spmm_core_ws_bytes(int32_t n_rows);

@@ -712,6 +712,17 @@ constexpr int kPieceMin = 56;                       // mean entries per piece of
 // passes), so no lane of a narrow product idles.
 inline int32_t blocked_width(int32_t d) { return d <= 16 ? 16 : d <= 32 ? 32 : kBlockW; }
 
+// the row list: the whole processing order, or the long rows
+inline size_t list_bytes(int32_t n_rows) {
+    return align_up(sizeof(int32_t) * (size_t)std::max(n_rows, 1), 256);
+}
+// bytes of the blocked mode's split points and partial rows for P ranges
+inline size_t blocked_bytes(int32_t n_rows, int32_t P) {
+    if (P <= 1) return 0;
+    return align_up(sizeof(int32_t) * (size_t)n_rows * (P + 1), 256) +
+           align_up(sizeof(float) * (size_t)P * n_rows * kBlockW, 256);
+}
+
 // Number of column ranges P for a product with n_rows rows, about nnz
 // entries, n_src distinct B rows referenced and d features; 1 = not blocked.
 // Blocked when the referenced slice of B one pass gathers from (the
@@ -732,9 +743,11 @@ inline int32_t blocked_width(int32_t d) { return d <= 16 ? 16 : d <= 32 ? 32 : k
 // (132,534 nodes, 600 entries per row, d = 256: 14 % of the gathers missed;
 // 4.68 ms with 8 ranges, 4.53 with 10, 4.49 with 12 of 50 entries each, 4.73
 // with 16). The narrower layouts and shorter rows lose by it (30 % of that
-// graph's columns: 1.53 ms with 3 ranges, 1.61 with 4).
+// graph's columns: 1.53 ms with 3 ranges, 1.61 with 4). Where the scratch of
+// rsc_spmm_noalloc holds the buffers of the 4.5 MiB ranges, no more ranges
+// than it holds, so that both calls give the same bits.
 // RSC_SPMM_BLOCKED=0 switches the mode off, =2..8 forces that P.
-inline int32_t column_blocks(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d, bool fine = true) {
+inline int32_t column_blocks(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d) {
     if (n_rows <= 0 || (int64_t)(kMaxBlocks + 1) * n_rows > INT32_MAX) return 1;  // virtual rows are int32
     if (const char *env = getenv("RSC_SPMM_BLOCKED")) {
         const int v = atoi(env);
@@ -746,9 +759,14 @@ inline int32_t column_blocks(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t
     if (P < 2 || P > 2 * kCoarseBlocks) return 1;
     P = std::min<int64_t>(P, kCoarseBlocks);
     if (nnz < (int64_t)kPieceMin * (kBlockW / W) * P * n_rows) return 1;
-    if (fine && W == kBlockW) {
+    if (W == kBlockW) {
         const int64_t r = (int64_t)std::ceil((double)n_src * W * 4 / kFineBytes);
-        P = std::max(P, std::min<int64_t>({r, kMaxBlocks, nnz / ((int64_t)kPieceMin * n_rows)}));
+        const int64_t fine = std::max(P, std::min<int64_t>({r, kMaxBlocks, nnz / ((int64_t)kPieceMin * n_rows)}));
+        const auto in_scratch = [&](int64_t p) {
+            return spmm_blocked_fits(n_rows, (int32_t)p) <= kNoallocScratchBytes;
+        };
+        const bool coarse_fits = in_scratch(P);
+        while (P < fine && (!coarse_fits || in_scratch(P + 1))) ++P;
     }
     return (int32_t)P;
 }
@@ -816,17 +834,6 @@ __global__ __launch_bounds__(256) void combine_blocks_kernel(const float *__rest
     }
 }
 
-}  // namespace
-
-namespace {
-// the row list: the whole processing order, or the long rows
-size_t list_bytes(int32_t n_rows) { return align_up(sizeof(int32_t) * (size_t)std::max(n_rows, 1), 256); }
-// bytes of the blocked mode's split points and partial rows for P ranges
-size_t blocked_bytes(int32_t n_rows, int32_t P) {
-    if (P <= 1) return 0;
-    return align_up(sizeof(int32_t) * (size_t)n_rows * (P + 1), 256) +
-           align_up(sizeof(float) * (size_t)P * n_rows * kBlockW, 256);
-}
 }  // namespace
 
 int32_t spmm_column_blocks(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d) {
@@ -932,10 +939,8 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     // The blocked mode is chosen from the expected entries and referenced B
     // rows (the same for the exact product and a full-budget slice of it);
     // it runs only when the workspace holds its buffers.
-    int32_t P = column_blocks(n_rows, nnz_hint, n_src_hint, d);
+    const int32_t P = column_blocks(n_rows, nnz_hint, n_src_hint, d);
     const size_t head = sizeof(SpmmWs) + list_bytes(n_rows);
-    if (P > 1 && head + blocked_bytes(n_rows, P) > ws_bytes)  // a fixed scratch may hold the coarser ranges
-        P = column_blocks(n_rows, nnz_hint, n_src_hint, d, false);
     if (P > 1 && head + blocked_bytes(n_rows, P) <= ws_bytes) {
         char *p = static_cast<char *>(ws) + head;
         float *part = reinterpret_cast<float *>(p + align_up(sizeof(int32_t) * (size_t)n_rows * (P + 1), 256));

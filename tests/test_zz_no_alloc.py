@@ -80,6 +80,23 @@ def test_blocked_product_in_scratch_and_unblocked_fallback():
     assert np.array_equal(Yn.view(np.uint32), Yw.view(np.uint32))
 
 
+@pytest.mark.parametrize("n_rows,n_cols,row_len", [
+    (40_000, 40_000, 230),     # 3 ranges of 3.3 MB; buffers of a fourth would not fit
+    (14_000, 160_000, 1000),   # 9 ranges; ranges of 3 MiB, 12 of them, would not fit
+    (12_000, 160_000, 1000),   # 10
+    (2_000, 160_000, 1000),    # all 12 fit
+])
+def test_equal_wherever_blocked_buffers_fit(n_rows, n_cols, row_len):
+    """The finer column ranges stop where the scratch does, so the same
+    ranges and bits come out with and without a workspace."""
+    A, B = _case(np.full(n_rows, row_len), n_cols, 72, 51)
+    Yn, Yw = _both(A, B, n_cols)
+    assert np.array_equal(Yn.view(np.uint32), Yw.view(np.uint32))
+    rows = np.arange(0, n_rows, 97, dtype=np.int32)
+    Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, rows=rows, with_mag=True)
+    assert rel_err(Yn[rows], Yo, S) <= 1e-5
+
+
 def test_rejects_products_beyond_the_scratch():
     L = rsc.lib()
     s = rsc.CsrStruct(9_000_000, 1000, 0, 0x1000, 0, 0)   # 9M rows: 36 MB of row list
