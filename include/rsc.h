@@ -152,8 +152,7 @@ rsc_status_t rsc_spmm_noalloc(const rsc_csr_t *A, const float *B, int32_t d, int
  *   - its own workspace, so runs need none;
  *   - when the product runs column-blocked, the split bounds of the rows
  *     (for the range count of feature widths above 32; a run at a width
- *     whose range count differs builds its own, as rsc_spmm does, and so
- *     does every later run of the plan);
+ *     whose range count differs builds its own, as rsc_spmm does);
  *   - the long-row list (or the length-class row order) and its length,
  *     which every rsc_spmm call builds first;
  *   - for operands with more than 262,144 columns, a copy of col whose bit
@@ -339,8 +338,7 @@ rsc_status_t rsc_sample_columns(const uint64_t *key, int32_t n, int32_t k, uint6
  *     rsc_spmm; every row of Y' is written. Needs a refreshed cache. Each
  *     selection prepares the products for the feature width of the operand
  *     last scored (row list, or split bounds when column-blocked); a
- *     product of another width whose preparation differs builds its own,
- *     and so does every later product until the next selection. */
+ *     product of another width whose preparation differs builds its own. */
 typedef struct rsc_cache rsc_cache_t;
 rsc_status_t rsc_cache_create(const rsc_csr_t *X, const rsc_csr_t *XT, int32_t refresh_interval,
                               hipStream_t stream, rsc_cache_t **out);

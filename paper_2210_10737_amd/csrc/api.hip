@@ -421,7 +421,7 @@ rsc_status_t rsc_spmm_plan_create(const rsc_csr_t *A, hipStream_t stream, rsc_sp
     // the per-call preparation of the product, done once: split bounds
     // (column-blocked), or the long-row list / row order
     // (prepared for feature widths of 33 and more; a narrower product whose
-    // range count differs prepares for itself on every run)
+    // range count differs prepares for itself on each of its runs)
     const int32_t P = std::max(1, rsc::spmm_column_blocks(A->n_rows, A->nnz, A->n_cols, 64));
     {
         hipError_t e = hipSuccess;
@@ -491,16 +491,16 @@ rsc_status_t rsc_spmm_plan_run(rsc_spmm_plan_t *p, const float *B, int32_t d, in
     RSC_TRY(check_dense(B, A->n_cols, d, ldb, "B"));
     RSC_TRY(check_dense(Y, A->n_rows, d, ldy, "Y"));
     RSC_TRY(check_same_device(p->device, "plan"));
-    bool used = false;
+    bool listed_anew = false;
     hipEvent_t stop = nullptr;
     RSC_HIP(p->fence.event_for(stream, &stop), "plan run event");
     const hipError_t e = rsc::spmm_launch(A->n_rows, A->n_cols, A->nnz, A->rowptr, p->colf ? p->colf : A->col,
                                           A->val, B, d, ldb, Y, ldy, p->ws, p->ws_bytes, stream, A->nnz, A->n_cols,
-                                          p->colf != nullptr, &p->prep, &used, stop);
+                                          p->colf != nullptr, &p->prep, &listed_anew, stop);
     // a run whose decisions differed (an environment switch changed since the
-    // plan was made) rebuilt its own row list in the plan's workspace: from
-    // then on every run prepares for itself
-    if (!used && A->n_rows > 0) p->prep.ready = false;
+    // plan was made) built its row list over the plan's: from then on every
+    // run prepares for itself
+    if (listed_anew && p->prep.list) p->prep.ready = false;
     RSC_HIP(e, "plan run");
     return RSC_OK;
 }
@@ -950,13 +950,13 @@ rsc_status_t rsc_spmm_sampled(rsc_cache_t *c, const float *B, int32_t d, int64_t
     // never depend on which calls came before).
     const int64_t kk = std::min<int64_t>(c->k, c->n);
     const int64_t nnz_hint = c->n > 0 ? c->X.nnz * kk / c->n : 0;
-    bool used = false;
+    bool listed_anew = false;
     hipEvent_t stop = nullptr;
     RSC_HIP(c->fence.event_for(stream, &stop), "cache event");
     const hipError_t e = rsc::spmm_launch(c->X.n_rows, c->X.n_cols, c->X.nnz, c->s_rowptr, c->s_col, c->s_val, B, d,
                                           ldb, Y, ldy, c->ws_spmm, c->ws_spmm_bytes, stream, nnz_hint, kk, false,
-                                          &c->prep, &used, stop);
-    if (!used) c->prep.ready = false;  // the launch rebuilt its own list in ws_spmm
+                                          &c->prep, &listed_anew, stop);
+    if (listed_anew && c->prep.list) c->prep.ready = false;  // the launch's list lies over the prepared one
     RSC_HIP(e, "spmm_sampled launch");
     return RSC_OK;
 }

@@ -38,8 +38,10 @@ int32_t spmm_slice_width(int32_t n_rows, int64_t nnz, int64_t n_src, int32_t d);
 // with long_rows their count (-1: not known on the host) and ordered the
 // row-order decision taken; list says that the workspace holds the list (or
 // the order), without it long rows are taken by the blocks that hold them.
-// A launch uses them only while its own decisions match (ready); one that
-// did not (*used_prep false) rebuilt the list in that workspace.
+// A launch uses them only while its own decisions match (ready). One whose
+// decisions differ prepares for itself, in the workspace; *listed_anew says
+// that it built a list there, over the one prepared (the split bounds and
+// what else it writes lie elsewhere).
 struct SpmmPrepared {
     const int32_t *split = nullptr;
     int32_t P = 1;
@@ -52,7 +54,7 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
                        const int32_t *col, const float *val, const float *B, int32_t d, int64_t ldb, float *Y,
                        int64_t ldy, void *ws, size_t ws_bytes, hipStream_t stream, int64_t nnz_hint,
                        int64_t n_src_hint, bool hint_cols = false, const SpmmPrepared *prep = nullptr,
-                       bool *used_prep = nullptr, hipEvent_t stop = nullptr);
+                       bool *listed_anew = nullptr, hipEvent_t stop = nullptr);
 // The column-blocked mode's range count for a product (1 = not blocked) and
 // its split bounds S[(P + 1) * n_rows]; the row-order decision; and the
 // preparation a launch would do, run once into a plan's workspace (then

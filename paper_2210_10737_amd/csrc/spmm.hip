@@ -930,9 +930,9 @@ struct LongRows {
 hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const int32_t *rowptr,
                        const int32_t *col, const float *val, const float *B, int32_t d, int64_t ldb, float *Y,
                        int64_t ldy, void *ws, size_t ws_bytes, hipStream_t stream, int64_t nnz_hint,
-                       int64_t n_src_hint, bool hint_cols, const SpmmPrepared *prep, bool *used_prep,
+                       int64_t n_src_hint, bool hint_cols, const SpmmPrepared *prep, bool *listed_anew,
                        hipEvent_t stop) {
-    if (used_prep) *used_prep = false;
+    if (listed_anew) *listed_anew = false;
     if (n_rows == 0) return hipSuccess;
     SpmmWs *h = static_cast<SpmmWs *>(ws);
     int32_t *list = reinterpret_cast<int32_t *>(h + 1);  // long-row list, or the whole processing order
@@ -947,7 +947,6 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
         const int32_t nv = P * n_rows;  // virtual rows, block-major
         // split bounds: a plan's, prepared once, or this call's
         const bool pre = prep && prep->ready && prep->P == P && prep->split;
-        if (used_prep) *used_prep = pre;
         const int32_t *S = pre ? prep->split : reinterpret_cast<const int32_t *>(p);
         if (!pre) {
             const hipError_t e = spmm_split_launch(n_rows, n_cols, rowptr, col, P, reinterpret_cast<int32_t *>(p),
@@ -996,11 +995,11 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     // this workspace already; else it is built here, except over few rows,
     // whose long rows their blocks find
     const bool pre = prep && prep->ready && prep->P == 1 && prep->ordered == ordered;
-    if (used_prep) *used_prep = pre;
     LongRows lr;
     if (ordered || (long_rows_bound(n_rows, nnz_bound) > 0 && !(pre && prep->long_rows == 0))) {
         const bool listed = ordered || (pre ? prep->list : spmm_lists_long_rows(n_rows));
         if (listed && !pre) {
+            if (listed_anew) *listed_anew = true;
             const hipError_t e = spmm_rows_prepare(n_rows, nnz_bound, rowptr, ws, stream);
             if (e != hipSuccess) return e;
         }

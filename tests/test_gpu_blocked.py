@@ -6,6 +6,7 @@ graphs whose B slice (16, 32 or 64 floats per row, by feature width) spans
 caches used at several widths: exact and sampled SpMM
 against the oracle, a full-budget slice equal to the exact product bit for
 bit, and the automatic choice equal to the forced one."""
+import ctypes
 import os
 
 import numpy as np
@@ -233,3 +234,40 @@ def test_long_pieces_outnumber_rows(n_rows, n_cols, row_len, d):
     Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, with_mag=True)
     assert rel_err(Y.cpu().numpy(), Yo, S) <= 1e-5
     assert rel_err(Yu.cpu().numpy(), Yo, S) <= 1e-5
+
+
+def _launches(f):
+    """Nodes of the graph that f's launches are captured into."""
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        f()
+    n = ctypes.c_size_t()
+    assert rsc.lib().hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+def test_preparation_survives_other_widths():
+    # a run at a width with another range count splits the rows for itself;
+    # the next run at the prepared width has nothing to prepare, as before it
+    n_rows, n_cols = 500, 160_000
+    A = synth.bucket_csr(np.full(n_rows, 1000), n_cols, seed=35)
+    AT = synth.transpose(A, n_cols)
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n_cols)
+    XT = rsc.DeviceCsr.from_host(AT.rowptr, AT.col, AT.val, n_rows)
+    Bs = {d: torch.from_numpy(synth.dense_normal(n_cols, d, seed=36 + d)).cuda() for d in (16, 64)}
+    Y = {d: torch.empty((n_rows, d), device="cuda") for d in Bs}
+    with blocked(None):
+        plan, cache = rsc.SpmmPlan(X), rsc.Cache(X, XT)
+        cache.refresh(Bs[64], n_cols, step=0)
+        for run in (lambda d: plan.run(Bs[d], out=Y[d]), lambda d: cache.spmm_sampled(Bs[d], out=Y[d])):
+            run(64)
+            torch.cuda.synchronize()
+            assert [_launches(lambda: run(d)) for d in (64, 16, 64)] == [2, 3, 2]
+            run(16)
+            run(64)
+            for d in Bs:
+                assert torch.equal(Y[d], rsc.spmm(X, Bs[d])), d
+            torch.cuda.synchronize()
+            assert _launches(lambda: run(64)) == 2
+        plan.close()
+        cache.close()
