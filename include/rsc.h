@@ -261,7 +261,8 @@ rsc_status_t rsc_topk_select(const uint64_t *key, int32_t n, int32_t k, int32_t 
  * randomized sampler's 1/(k p) weighting needs.
  * nnz_out: device int64 receiving nnz'. The slice runs as a stream
  * compaction in four launches (a tile-to-row table, count, sums, emit; two for
- * up to 131,072 columns and 2,048 tiles of 4,096 entries;
+ * up to 131,072 columns and 2,048 tiles of 4,096 entries, and no more than
+ * 4,096 rows per tile;
  * RSC_SLICE_PAIRED=0 turns off the count's block pairing for masks of
  * 1.28M to 2.56M columns, which changes only its speed);
  * with the environment variable RSC_SLICE_FUSED=1 it runs as one fused

@@ -214,6 +214,11 @@ __global__ __launch_bounds__(kCoarse) void slice_coarse_kernel(uint32_t *__restr
 // the tile rows. One launch in place of two.
 constexpr int32_t kSmallWords = 4096;  // 131,072 columns
 constexpr int32_t kSmallTiles = 2048;
+// and at most so many rows per thread to mark: each costs its thread a wait,
+// and the row pass of the other form has threads for all of them (400,000
+// entries, us, this form / the other: 401,408 rows, 16 a thread, 18.8 / 22.1;
+// 32 a thread 25.3 / 23.8; 64 a thread 42.0 / 32.6)
+constexpr int32_t kSmallRowsPer = 16;
 
 __global__ __launch_bounds__(256) void slice_count_small_kernel(const int32_t *__restrict__ rowptr, int32_t n_rows,
                                                                 const int32_t *__restrict__ col, int64_t nnz,
@@ -633,7 +638,8 @@ hipError_t slice_launch(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32
             e = hipMemcpyAsync(nnz_host, nnz_out, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
         return e == hipSuccess && stop ? hipEventRecord(stop, stream) : e;
     }
-    const bool small = n_words > 0 && n_words <= kSmallWords && nt <= kSmallTiles;
+    const bool small = n_words > 0 && n_words <= kSmallWords && nt <= kSmallTiles &&
+                       n_rows <= (int64_t)kSmallRowsPer * 256 * nt;
     // a mask of two LDS pieces is tested by pairs of blocks (one piece each,
     // the same tiles at the same time), given whole groups of 16 blocks
     const int32_t n_pieces = (int32_t)ceil_div(std::max<int32_t>(n_words, 1), kMaskLdsWords);

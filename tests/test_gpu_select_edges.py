@@ -2,6 +2,8 @@
 thread block, counts added tile by tile or by groups of tiles, the small
 forms, and searches that end before the last digit. Bit for bit against torch
 or the oracle; everything here is integer or copied."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -74,6 +76,31 @@ def test_slice_sizes(n_cols, nnz):
     assert np.array_equal(S.rowptr.cpu().numpy(), ro)
     assert np.array_equal(S.col[:m].cpu().numpy(), co)
     assert np.array_equal(S.val[:m].cpu().numpy().view(np.uint32), vo.view(np.uint32))
+
+
+@pytest.mark.parametrize("n_rows,launches", [(4096, 2), (4097, 4), (8192, 2), (8193, 4), (300_000, 4)])
+def test_slice_of_mostly_empty_rows(n_rows, launches):
+    """The two-launch slice marks the rows with its tiles' threads, so more
+    rows than 4,096 a tile take the form with a pass of its own for them."""
+    n_cols, nnz = 5000, 4096 if n_rows < 5000 else 8192
+    lens = np.bincount(np.random.default_rng(n_rows).integers(0, n_rows, nnz), minlength=n_rows)
+    A = synth.bucket_csr(lens, n_cols, seed=n_rows % 1000)
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n_cols)
+    words = np.random.default_rng(1).integers(0, 1 << 32, (n_cols + 31) // 32, dtype=np.uint64).astype(np.uint32)
+    words[-1] &= np.uint32((1 << n_cols % 32) - 1)
+    mask = torch.from_numpy(words.view(np.int32)).cuda()
+    S, nnz_out = rsc.slice_csr(X, mask)
+    ro, co, vo = oracle.slice_csr(A.rowptr, A.col, A.val, words)
+    m = int(nnz_out.item())
+    assert m == len(co) and np.array_equal(S.rowptr.cpu().numpy(), ro)
+    assert np.array_equal(S.col[:m].cpu().numpy(), co)
+    assert np.array_equal(S.val[:m].cpu().numpy().view(np.uint32), vo.view(np.uint32))
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        rsc.slice_csr(X, mask)
+    n = ctypes.c_size_t()
+    assert rsc.lib().hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value == launches
 
 
 @pytest.mark.parametrize("n,d", [(1, 4), (63, 100), (65, 64), (64, 65), (65_536, 96), (65_536, 100), (65_537, 100), (70_001, 64)])
