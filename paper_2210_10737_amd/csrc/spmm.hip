@@ -114,11 +114,6 @@ __global__ __launch_bounds__(kCollectThreads) void collect_long_rows_kernel(
 // instruction. Lane L belongs to entry-group g = L / LPE and owns features
 // 4 * (L % LPE) .. +3 of the current feature slice (plus +256 for NV = 2,
 // which is only used with LPE = 64).
-template <int LPE>
-struct Layout {
-    static constexpr int G = kWave / LPE;
-    static_assert(kWave % LPE == 0, "LPE must divide the wave");
-};
 
 // ---- one entry per load instruction (LPE = 64) ----------------------------
 // Accumulates runs of 64 entries starting at beg, beg + stride, ... (< end)
@@ -291,6 +286,11 @@ __device__ __forceinline__ void run_blocks(const Operand &op, const Run<LPE> &ru
     if constexpr (BLK + 1 < NB) run_blocks<LPE, NB, BLK + 1>(op, run, b1, b0, a, behind);
 }
 
+__device__ __forceinline__ void fold(const float (&a)[4], double (&acc)[4]) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) acc[x] += (double)a[x];
+}
+
 // The run's first nb blocks (1 <= nb <= kBlocks, wave-uniform).
 template <int LPE, int NB = 1>
 __device__ __forceinline__ void run_first(const Operand &op, const Run<LPE> &run, int32_t nb, float (&a)[4]) {
@@ -304,11 +304,13 @@ __device__ __forceinline__ void run_first(const Operand &op, const Run<LPE> &run
 
 // Sums the entries of runs beg, beg + stride, ... (< end; stride >= 64, beg <
 // end): each group's fp32 sum over its share of a run is folded into the
-// lane's fp64 acc. Every run but the last is whole.
+// lane's fp64 acc, but for the last run's, which is left in `last`. Every run
+// but the last is whole.
 template <int LPE>
 __device__ __forceinline__ void accumulate_groups(const int32_t *__restrict__ col, const float *__restrict__ val,
                                                   const Operand &op, uint32_t ldb_bytes, int64_t beg,
-                                                  int64_t end, int32_t stride, int lane, double (&acc)[4]) {
+                                                  int64_t end, int32_t stride, int lane, double (&acc)[4],
+                                                  float (&last)[4]) {
     using R = Run<LPE>;
     constexpr int kPairEntries = R::kPairSteps * R::kGroups;
     // lane that loaded this lane's entry of a run (pair q's is kPairEntries further on)
@@ -331,10 +333,6 @@ __device__ __forceinline__ void accumulate_groups(const int32_t *__restrict__ co
             run.v[q] = __shfl(v, e0 + q * kPairEntries);
         }
     };
-    const auto fold = [&](const float(&a)[4]) {
-#pragma unroll
-        for (int x = 0; x < 4; ++x) acc[x] += (double)a[x];
-    };
     load(beg);
     int64_t base = beg;  // int64: base + stride may pass 2^31 - 1
     for (; base + stride < end; base += stride) {
@@ -342,13 +340,11 @@ __device__ __forceinline__ void accumulate_groups(const int32_t *__restrict__ co
         float a[4] = {0.f, 0.f, 0.f, 0.f};
         vf4 b0[4], b1[4];
         run_blocks<LPE, R::kBlocks>(op, run, b0, b1, a, [&] { load(base + stride); });
-        fold(a);
+        fold(a, acc);
     }
     take(base, false);
-    float a[4] = {0.f, 0.f, 0.f, 0.f};
     const int32_t left = __builtin_amdgcn_readfirstlane((int32_t)min<int64_t>(kWave, end - base));
-    run_first<LPE>(op, run, (left + 4 * R::kGroups - 1) / (4 * R::kGroups), a);
-    fold(a);
+    run_first<LPE>(op, run, (left + 4 * R::kGroups - 1) / (4 * R::kGroups), last);
 }
 
 // The same sums with 64-bit addresses and a lane mask per step; kHint as in
@@ -357,10 +353,13 @@ template <int LPE, bool kHint>
 __device__ __forceinline__ void accumulate_groups_wide(const int32_t *__restrict__ col,
                                                        const float *__restrict__ val, const float *__restrict__ B,
                                                        int64_t ldb, int64_t beg, int64_t end, int32_t stride,
-                                                       bool act, int lane, double (&acc)[4]) {
+                                                       bool act, int lane, double (&acc)[4], float (&last)[4]) {
     constexpr int G = kWave / LPE;
+    constexpr int kSteps = kWave / G;           // steps that cover the 64-entry run
+    constexpr int kWin = G >= 8 ? 4 : kUnroll;  // steps per window (gathers in flight)
     const int g = lane / LPE, sl = lane % LPE;
     for (int64_t base = beg; base < end; base += stride) {
+        if (base > beg) fold(last, acc);
         const int32_t cnt = __builtin_amdgcn_readfirstlane((int32_t)min<int64_t>(kWave, end - base));
         int32_t my_c = 0;
         float my_v = 0.f;
@@ -369,40 +368,42 @@ __device__ __forceinline__ void accumulate_groups_wide(const int32_t *__restrict
             my_v = __builtin_nontemporal_load(val + base + lane);
         }
         float a[4] = {0.f, 0.f, 0.f, 0.f};
-                    constexpr int kSteps = kWave / G;  // steps that cover the 64-entry run
-                    constexpr int kWin = G >= 8 ? 4 : kUnroll;  // steps per window (gathers in flight)
-                    // one window of kUnroll steps at a time: unrolling the step loop
-                    // too keeps every window's (col, val) live at once (130 VGPRs for
-                    // G = 2) and costs occupancy
-        #pragma unroll 1
-                    for (int t0 = 0; t0 < kSteps; t0 += kWin) {
-                        if (t0 * G >= cnt) break;  // wave-uniform
-                        float4 b[kWin];
-                        float v[kWin];
-        #pragma unroll
-                        for (int u = 0; u < kWin; ++u) {
-                            const int j = (t0 + u) * G + g;  // entry of this group within the run
-                            const int32_t cf = __shfl(my_c, j & (kWave - 1));
-                            const int32_t c = cf & kColMask;
-                            const float vv = __shfl(my_v, j & (kWave - 1));
-                            b[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                            v[u] = 0.f;
-                            if (t0 + u < kSteps && j < cnt && act) {
-                                const float4 *brow = reinterpret_cast<const float4 *>(B + (int64_t)c * ldb) + sl;
-                                b[u] = (kHint && cf >= 0) ? load_nt(brow) : *brow;
-                                v[u] = vv;
-                            }
-                        }
-        #pragma unroll
-                        for (int u = 0; u < kWin; ++u) {
-                            a[0] = fmaf(v[u], b[u].x, a[0]);
-                            a[1] = fmaf(v[u], b[u].y, a[1]);
-                            a[2] = fmaf(v[u], b[u].z, a[2]);
-                            a[3] = fmaf(v[u], b[u].w, a[3]);
-                        }
-                    }
+        // one window at a time: unrolling the step loop too keeps every
+        // window's (col, val) live at once (130 VGPRs for G = 2) and costs
+        // occupancy
+#pragma unroll 1
+        for (int t0 = 0; t0 < kSteps; t0 += kWin) {
+            if (t0 * G >= cnt) break;  // wave-uniform
+            float4 b[kWin];
+            float v[kWin];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) acc[x] += (double)a[x];
+            for (int u = 0; u < kWin; ++u) {
+                const int j = (t0 + u) * G + g;  // entry of this group within the run
+                const int32_t cf = __shfl(my_c, j & (kWave - 1));
+                const int32_t c = cf & kColMask;
+                const float vv = __shfl(my_v, j & (kWave - 1));
+                const bool in = t0 + u < kSteps && j < cnt && act;
+                // selected out here: set inside the branch, the compiler had
+                // each window's first gather waited for before the others were
+                // issued (1,500,000 rows of 3 entries, d = 96, hinted: 657 us
+                // against 570)
+                v[u] = in ? vv : 0.f;
+                b[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (in) {
+                    const float4 *brow = reinterpret_cast<const float4 *>(B + (int64_t)c * ldb) + sl;
+                    b[u] = (kHint && cf >= 0) ? load_nt(brow) : *brow;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kWin; ++u) {
+                a[0] = fmaf(v[u], b[u].x, a[0]);
+                a[1] = fmaf(v[u], b[u].y, a[1]);
+                a[2] = fmaf(v[u], b[u].z, a[2]);
+                a[3] = fmaf(v[u], b[u].w, a[3]);
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) last[x] = a[x];
     }
 }
 
@@ -416,11 +417,13 @@ __device__ __forceinline__ void sum_groups(T (&a)[4]) {
         for (int x = 0; x < 4; ++x) a[x] += __shfl_xor(a[x], m);
 }
 
-// What a wave accumulates for one row with either kind of layout.
+// What a wave accumulates for one row with either kind of layout; in the
+// sliced ones the last run's sums are left in `last`.
 template <int LPE, int NV, bool kHint, bool kBuf>
 __device__ __forceinline__ void accumulate(const int32_t *__restrict__ col, const float *__restrict__ val,
                                            const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, int64_t beg,
-                                           int64_t end, int32_t stride, int32_t d, int lane, double (&acc)[NV][4]) {
+                                           int64_t end, int32_t stride, int32_t d, int lane, double (&acc)[NV][4],
+                                           float (&last)[4]) {
     if constexpr (LPE == kWave) {
         bool act[NV];
 #pragma unroll
@@ -435,17 +438,17 @@ __device__ __forceinline__ void accumulate(const int32_t *__restrict__ col, cons
             Operand op;
             op.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(B), 0, b_bytes, 0x00027000);
             op.lane_off = 16u * min(lane % LPE, (d - 1) / 4);
-            if (beg < end) accumulate_groups<LPE>(col, val, op, (uint32_t)(4 * ldb), beg, end, stride, lane, acc[0]);
+            if (beg < end)
+                accumulate_groups<LPE>(col, val, op, (uint32_t)(4 * ldb), beg, end, stride, lane, acc[0], last);
         } else {
             accumulate_groups_wide<LPE, kHint>(col, val, B, ldb, beg, end, stride, 4 * (lane % LPE) < d, lane,
-                                               acc[0]);
+                                               acc[0], last);
         }
     }
 }
 
-template <int LPE, int NV>
-__device__ __forceinline__ void store_row(float *__restrict__ yrow, int32_t d, int lane,
-                                          const double (&acc)[NV][4]) {
+template <int LPE, int NV, typename T>
+__device__ __forceinline__ void store_row(float *__restrict__ yrow, int32_t d, int lane, const T (&acc)[NV][4]) {
     if (lane >= LPE) return;  // every entry-group holds the same sums; group 0 stores
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
@@ -469,8 +472,10 @@ __device__ __forceinline__ void take_long_row(const int32_t *__restrict__ col, c
     double acc[NV][4];
 #pragma unroll
     for (int q = 0; q < NV; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
+    float last[4] = {0.f, 0.f, 0.f, 0.f};
     accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, (int64_t)s + kWave * wave, e, kWave * kWaves, d, lane,
-                                     acc);
+                                     acc, last);
+    if constexpr (LPE < kWave) fold(last, acc[0]);
     // opaque: what derives from the lane below is computed here and not kept
     // in registers through the gathers
     asm volatile("" : "+v"(lane));
@@ -567,18 +572,26 @@ __global__ __launch_bounds__(kWaves * 64) void spmm_kernel(
         double acc[NV][4];
 #pragma unroll
         for (int q = 0; q < NV; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
-        accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, s, e, kWave, d, lane, acc);
+        float last[1][4] = {{0.f, 0.f, 0.f, 0.f}};
+        accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, s, e, kWave, d, lane, acc, last[0]);
         if constexpr (LPE < kWave) {
-            if (e - s <= kWave) {  // one run: acc holds fp32 sums, which are added in fp32
-                float a[4] = {(float)acc[0][0], (float)acc[0][1], (float)acc[0][2], (float)acc[0][3]};
-                sum_groups<LPE>(a);
+            // One run: its fp32 sums are added and stored as they are (through
+            // fp64 and back, 1,500,000 rows of 3 entries, d = 32, took 415 us
+            // in place of 400). A negative zero becomes the positive one that
+            // the fp64 sums give.
+            if (e - s <= kWave) {
+                sum_groups<LPE>(last[0]);
 #pragma unroll
-                for (int x = 0; x < 4; ++x) acc[0][x] = a[x];
+                for (int x = 0; x < 4; ++x) last[0][x] += 0.f;
+                store_row<LPE, 1>(Y + (int64_t)r * ldy, d, lane, last);
             } else {
+                fold(last[0], acc[0]);
                 sum_groups<LPE>(acc[0]);
+                store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
             }
+        } else {
+            store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
         }
-        store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
     }
     if constexpr (kCoop)
         for (; longs; longs &= longs - 1) take_long(first + __builtin_ctz(longs));  // block-uniform
