@@ -50,8 +50,11 @@ constexpr int kSpmmWaves = 4;          // waves per block, and short rows
 // units without a block, and at 512 features 8 waves cost 13 %.
 constexpr int32_t kWideBlockRows = 16384;
 constexpr int32_t kWideBlockMean = 32;
+constexpr int kCoopWindow = 1024;      // blocks that share out the long rows among theirs
 constexpr int kSpmmLongBlocks = 1024;  // blocks that walk a long-row list of unknown length
-constexpr int kSpmmLongBlocksMax = 8192;  // blocks for a list of known length (one row each up to here)
+constexpr int kSpmmLongBlocksMax = 8192;  // blocks for a list of known length (one row each up to here), or to look for the rows
+constexpr int32_t kListedRows = 262144;  // from here on an unplanned product lists its long rows
+static_assert(kListedRows <= kSpmmLongBlocksMax * kSpmmWaves * kWave, "a thread for each row that is looked at");
 
 namespace {
 
@@ -503,11 +506,19 @@ __device__ __forceinline__ void take_long_row(const int32_t *__restrict__ col, c
 // at the first feature of the current slice; d is its width.
 //
 // Blocks from n_long on take kWaves consecutive rows, one wave each. Long
-// rows are a block's work, by one of two ways:
-//   * a list (!kCoop): the first n_long blocks walk the prepared list of long
-//     rows (or the head of `order`), so that the heaviest rows start first;
-//   * kCoop (nothing prepared, n_long = 0): a block that finds long rows among
-//     its own takes them with all its waves when its short rows are done.
+// rows are a block's work, by one of three ways:
+//   * a list: the first n_long blocks walk the prepared list of long rows (or
+//     the head of `order`), so that the heaviest rows start first;
+//   * no list (NULL; nothing prepared): each of the first n_long blocks looks
+//     through every n_long-th row and takes the long ones it finds. Long rows
+//     side by side (nodes sorted by degree) so go to as many blocks;
+//   * kCoop (column-blocked, n_long = 0): a block looks at every step-th row of
+//     a window of kCoopWindow blocks' rows, and takes the long ones when its
+//     short rows are done. A window is about what the chip holds at once, so a
+//     long piece reads the range of B that its neighbours read.
+// (Blocks that took the long ones of their own rows: 60,013 rows, mean 27,
+// hubs of 30,000 entries in the first rows, d = 41: 426 us, against 131; d =
+// 128: 758, against 255.)
 // With `order`, the rows are taken in that order after its first *long_count
 // entries (the long rows). Which block takes a row never changes its sum.
 // (Long rows in a launch of their own before the others left the chip to its
@@ -526,7 +537,7 @@ __global__ __launch_bounds__(kWaves * 64) void spmm_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const auto take_long = [&](int32_t r) {
         const int32_t s = __builtin_amdgcn_readfirstlane(ptr[r]);
-        const int32_t e = __builtin_amdgcn_readfirstlane(kCsr ? ptr[r + 1] : ptr[(int64_t)r + off]);
+        const int32_t e = __builtin_amdgcn_readfirstlane(ptr[(int64_t)r + (kCsr ? 1 : off)]);
         int ln = lane;
         asm volatile("" : "+v"(ln));  // as in take_long_row
         take_long_row<LPE, NV, kHint, kBuf, kWaves>(col, val, B, ldb, b_bytes, Y + (int64_t)r * ldy, d, s, e, ln,
@@ -535,38 +546,49 @@ __global__ __launch_bounds__(kWaves * 64) void spmm_kernel(
     const int32_t bid = blockIdx.x;
     if constexpr (!kCoop) {
         if (bid < n_long) {
-            const int32_t n_list = __builtin_amdgcn_readfirstlane(*long_count);
-            for (int32_t j = bid; j < n_list; j += n_long) take_long(__builtin_amdgcn_readfirstlane(list[j]));
+            __shared__ int32_t found[kWaves * kWave];
+            __shared__ int32_t n_found;
+            if (!list) {  // n_long * kWaves * kWave >= n_rows
+                if (threadIdx.x == 0) n_found = 0;
+                __syncthreads();
+                const int32_t q = bid + n_long * threadIdx.x;
+                if (q < n_rows && ptr[q + 1] - ptr[q] > kLongRow) found[atomicAdd(&n_found, 1)] = q;
+                __syncthreads();
+            }
+            const int32_t n_list = __builtin_amdgcn_readfirstlane(list ? *long_count : n_found);
+            for (int32_t j = list ? bid : 0; j < n_list; j += list ? n_long : 1)
+                take_long(__builtin_amdgcn_readfirstlane(list ? list[j] : found[j]));
             return;
         }
     }
     const int32_t first = (kCoop ? bid : bid - n_long) * kWaves;  // the block's first row
     int32_t r = first + wave, s = 0, e = 0;
-    uint32_t longs = 0;  // the block's own long rows
     if (!kCoop && ordered) {
         const int64_t i = (int64_t)__builtin_amdgcn_readfirstlane(*long_count) + r;
         if (i >= n_rows) return;
         r = __builtin_amdgcn_readfirstlane(list[i]);
     }
-    if (kCoop && first + kWaves <= n_rows) {
-        // the bounds of all the block's rows, in one round of scalar loads:
-        // every wave finds the same long rows
+    const auto end_of = [&](int32_t row) { return ptr[(int64_t)row + (kCsr ? 1 : off)]; };
+    // the block's share of its window's long rows: every wave finds the same
+    uint32_t longs = 0;
+    int32_t long0 = 0, step = 0;
+    if constexpr (kCoop) {
+        const int32_t w0 = bid / kCoopWindow * kCoopWindow;
+        step = min(kCoopWindow, (int32_t)gridDim.x - w0);
+        long0 = w0 * kWaves + (bid - w0);
+        int32_t len[kWaves];  // in one round of scalar loads
 #pragma unroll
         for (int i = 0; i < kWaves; ++i) {
-            const int32_t si = ptr[first + i], ei = ptr[(int64_t)first + i + (kCsr ? 1 : off)];
-            if (ei - si > kLongRow) longs |= 1u << i;
-            if (wave == i) s = si, e = ei;
+            const int32_t q = min(long0 + i * step, n_rows - 1);
+            len[i] = end_of(q) - ptr[q];
         }
-    } else {
-        if (kCoop)  // the last block
-            for (int i = 0; first + i < n_rows; ++i)
-                if (ptr[(int64_t)first + i + (kCsr ? 1 : off)] - ptr[first + i] > kLongRow) longs |= 1u << i;
-        if (r < n_rows) {
-            s = __builtin_amdgcn_readfirstlane(ptr[r]);
-            e = __builtin_amdgcn_readfirstlane(kCsr ? ptr[r + 1] : ptr[(int64_t)r + off]);
-        } else if (longs == 0) {
-            return;
-        }
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i)
+            if (len[i] > kLongRow && long0 + i * step < n_rows) longs |= 1u << i;
+    }
+    if (r < n_rows) {
+        s = __builtin_amdgcn_readfirstlane(ptr[r]);
+        e = __builtin_amdgcn_readfirstlane(end_of(r));
     }
     if (r < n_rows && !((kCoop || n_long > 0) && e - s > kLongRow)) {
         double acc[NV][4];
@@ -594,7 +616,7 @@ __global__ __launch_bounds__(kWaves * 64) void spmm_kernel(
         }
     }
     if constexpr (kCoop)
-        for (; longs; longs &= longs - 1) take_long(first + __builtin_ctz(longs));  // block-uniform
+        for (; longs; longs &= longs - 1) take_long(long0 + __builtin_ctz(longs) * step);  // block-uniform
 }
 
 // Bytes of B that a pass over dl features may read, counted from the first
@@ -927,18 +949,13 @@ size_t spmm_blocked_fits(int32_t n_rows, int32_t P) {
 const int32_t *spmm_long_count_of(const void *ws) { return &static_cast<const SpmmWs *>(ws)->long_count; }
 
 // Whether a product without a plan lists its long rows first (two launches,
-// about 10 us) or leaves them to the blocks that hold them, whose search for
-// them costs rows of ten entries about 8 % (2,094,669 nodes, mean 10, d = 23:
-// 0.83 ms against 0.75 with the list) and nothing on few rows (60,013 nodes,
-// mean 27, d = 41: 52 us against 70).
-bool spmm_lists_long_rows(int32_t n_rows) { return n_rows >= 262144; }
-
-namespace {
-struct LongRows {
-    int32_t n_long = 0;  // blocks that walk the list
-    int32_t coop = 0;    // no list: the blocks look for their own
-};
-}  // namespace
+// about 10 us) or leaves it to the first blocks to look for them.
+// Looking costs a block a round trip, listing the launches (us, looked for /
+// listed: 262,144 rows, mean 3, d = 23 84 / 89, mean 27, d = 256 1,058 / 1,055;
+// 500,000 rows, mean 10, d = 64 196 / 200; 1,000,000 rows, mean 10, d = 256
+// 1,726 / 1,696; 2,000,000 rows, mean 10, d = 256 3,940 / 3,876): level from
+// about 500,000 rows on, and under 2 % apart but for short rows below that.
+bool spmm_lists_long_rows(int32_t n_rows) { return n_rows >= kListedRows; }
 
 hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const int32_t *rowptr,
                        const int32_t *col, const float *val, const float *B, int32_t d, int64_t ldb, float *Y,
@@ -1005,10 +1022,10 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     }
     const bool ordered = use_order(n_rows, nnz_bound);
     // a plan's row list (long rows, or the whole order) prepared once sits in
-    // this workspace already; else it is built here, except over few rows,
-    // whose long rows their blocks find
+    // this workspace already; else it is built here, except over few rows
     const bool pre = prep && prep->ready && prep->P == 1 && prep->ordered == ordered;
-    LongRows lr;
+    int32_t n_long = 0;  // blocks that take the long rows
+    const int32_t *rows = nullptr;  // their list (or the order); NULL: they look for them
     if (ordered || (long_rows_bound(n_rows, nnz_bound) > 0 && !(pre && prep->long_rows == 0))) {
         const bool listed = ordered || (pre ? prep->list : spmm_lists_long_rows(n_rows));
         if (listed && !pre) {
@@ -1016,12 +1033,15 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
             const hipError_t e = spmm_rows_prepare(n_rows, nnz_bound, rowptr, ws, stream);
             if (e != hipSuccess) return e;
         }
-        if (!listed)
-            lr.coop = 1;
+        if (listed) rows = list;
+        const int64_t bound = long_rows_bound(n_rows, nnz_bound);
+        if (!listed)  // at least a thread for each row
+            n_long = (int32_t)std::min<int64_t>(std::max(bound, ceil_div(n_rows, kSpmmWaves * kWave)),
+                                                kSpmmLongBlocksMax);
         else if (pre && prep->long_rows >= 0)
-            lr.n_long = std::min(prep->long_rows, kSpmmLongBlocksMax);
+            n_long = std::min(prep->long_rows, kSpmmLongBlocksMax);
         else
-            lr.n_long = (int32_t)std::min<int64_t>(long_rows_bound(n_rows, nnz_bound), kSpmmLongBlocks);
+            n_long = (int32_t)std::min<int64_t>(bound, kSpmmLongBlocks);
     }
     const int32_t slice = spmm_slice_width(n_rows, nnz_hint, n_src_hint, d);
     // the hint pays off only when the gathered rows far outgrow the on-chip
@@ -1031,18 +1051,10 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     for (int32_t f0 = 0; f0 < d;) {
         const int32_t dl = std::min<int32_t>(d - f0, slice);
         const uint32_t bb = buffer_bytes(n_cols, ldb, dl);
-#define RSC_SPMM_LAUNCH_W(LPE_, NV_, H_, BUF_, COOP_, W_)                                              \
-    launch(spmm_kernel<LPE_, NV_, true, H_, BUF_, COOP_, W_>,                                          \
-           (unsigned)(lr.n_long + ceil_div(n_rows, W_)), W_ * 64, stream, f0 + dl >= d ? stop : nullptr, \
-           rowptr, (int64_t)1, col, val, B + f0, ldb, bb, Y + f0, ldy, n_rows, dl, lr.n_long,          \
-           (const int32_t *)list, (int32_t)(ordered ? 1 : 0), (const int32_t *)&h->long_count)
-#define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_, BUF_, W_)                  \
-    do {                                                            \
-        if (lr.coop)                                                \
-            RSC_SPMM_LAUNCH_W(LPE_, NV_, H_, BUF_, true, W_);       \
-        else                                                        \
-            RSC_SPMM_LAUNCH_W(LPE_, NV_, H_, BUF_, false, W_);      \
-    } while (0)
+#define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_, BUF_, W_)                                                     \
+    launch(spmm_kernel<LPE_, NV_, true, H_, BUF_, false, W_>, (unsigned)(n_long + ceil_div(n_rows, W_)), \
+           W_ * 64, stream, f0 + dl >= d ? stop : nullptr, rowptr, (int64_t)1, col, val, B + f0, ldb, bb, \
+           Y + f0, ldy, n_rows, dl, n_long, rows, (int32_t)(ordered ? 1 : 0), (const int32_t *)&h->long_count)
 #define RSC_SPMM_LAUNCH_SLICED(LPE_)                                \
     do {                                                            \
         if (hint)                                                   \
@@ -1070,7 +1082,6 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
                 if (hint) RSC_SPMM_LAUNCH_ROW(true); else RSC_SPMM_LAUNCH_ROW(false);
         }
 #undef RSC_SPMM_LAUNCH_ROW
-#undef RSC_SPMM_LAUNCH_W
 #undef RSC_SPMM_LAUNCH_SLICED
 #undef RSC_SPMM_LAUNCH_H
         f0 += dl;

@@ -117,3 +117,85 @@ def test_wide_blocks():
     assert torch.equal(rsc.spmm(X1, Bd)[short], Y[:-1][short])   # a short row is one wave's in both
     Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, with_mag=True)
     assert np.max(np.abs(Y.cpu().numpy().astype(np.float64) - Yo) / np.maximum(S, FLT_MIN)) <= 66 * 2.0 ** -24
+
+
+def _side_by_side(n_rows, first, count, n_cols, seed):
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 4, n_rows)
+    lens[first:first + count] = rng.integers(1025, 1400, count)
+    return synth.bucket_csr(lens, n_cols, seed=seed)
+
+
+@pytest.mark.parametrize("n_rows,first,count", [
+    (5000, 0, 600),              # more blocks look than there are groups of 256 rows
+    (4099, 4000, 99),            # up to the last row
+    (262_143, 262_043, 100),     # the most rows that are looked at, one a thread
+    (262_144, 262_044, 100),     # the fewest that are listed
+    (70_000, 0, 8),
+])
+@pytest.mark.parametrize("d", [30, 100, 200, 300])
+def test_long_rows_side_by_side(n_rows, first, count, d):
+    """Long rows in one run of rows: found by the blocks that look for them,
+    listed, or from a plan, the same bits, and the oracle's values."""
+    n_cols = 3000
+    A = _side_by_side(n_rows, first, count, n_cols, seed=n_rows % 1000 + d)
+    B = synth.dense_normal(n_cols, d, seed=62, ld=(d + 3) // 4 * 4)
+    Bd = torch.from_numpy(B).cuda()
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n_cols)
+    Y = rsc.spmm(X, Bd, d=d)
+    plan = rsc.SpmmPlan(X)
+    assert torch.equal(plan.run(Bd, d=d), Y)
+    plan.close()
+    rows = np.unique(np.r_[np.arange(first, first + count), np.arange(0, n_rows, 211)]).astype(np.int32)
+    Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, rows=rows, d=d, with_mag=True)
+    err = np.max(np.abs(Y.cpu().numpy()[rows].astype(np.float64) - Yo) / np.maximum(S, FLT_MIN))
+    assert err <= 66 * 2.0 ** -24   # a 64-entry fp32 chain at most, then fp64
+
+
+@pytest.mark.parametrize("d", [16, 32, 64])
+def test_long_pieces_side_by_side(d):
+    """Column-blocked: long pieces in a run of rows, over the edges of the
+    windows that share them out and in the last, partial one."""
+    n_cols = 4000
+    lens = np.random.default_rng(5).integers(0, 40, 5001)
+    lens[1000:1300] = 3500
+    lens[4980:] = 3300
+    A = synth.bucket_csr(lens, n_cols, seed=63)
+    B = synth.dense_normal(n_cols, d, seed=64)
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n_cols)
+    old = os.environ.get("RSC_SPMM_BLOCKED")
+    os.environ["RSC_SPMM_BLOCKED"] = "2"
+    try:
+        Y = rsc.spmm(X, torch.from_numpy(B).cuda()).cpu().numpy()
+    finally:
+        os.environ.pop("RSC_SPMM_BLOCKED") if old is None else os.environ.update(RSC_SPMM_BLOCKED=old)
+    Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, with_mag=True)
+    # as above, and each of the two partial rows rounded once
+    assert np.max(np.abs(Y.astype(np.float64) - Yo) / np.maximum(S, FLT_MIN)) <= 67 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("d", [41, 256])
+def test_sorted_hubs_cost_what_scattered_ones_cost(d):
+    """Rows sorted by length put the hubs side by side; without a plan they
+    must still go to as many blocks as the same rows in any order (in as many
+    blocks as four rows fill, they took three and a half times as long)."""
+    n = 60_013
+    lens = np.minimum(16.0 * ((np.arange(n) + 0.5) / n) ** (-1 / 1.1) / 7, 30_000).astype(np.int64) + 1
+    B = torch.from_numpy(synth.dense_normal(n, (d + 3) // 4 * 4, seed=7)).cuda()
+    times = []
+    for order in (np.arange(n), np.random.default_rng(2).permutation(n)):
+        A = synth.bucket_csr(lens[order], n, seed=8)
+        X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n)
+        ws = torch.empty(rsc.spmm_workspace_bytes(X), dtype=torch.uint8, device="cuda")
+        Y = rsc.spmm(X, B, d=d, ws=ws)
+        best = float("inf")
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(4):
+                rsc.spmm(X, B, d=d, out=Y, ws=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    assert times[0] <= 1.6 * times[1], times
