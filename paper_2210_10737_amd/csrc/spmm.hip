@@ -10,7 +10,8 @@
 //     coalesced, non-temporal load and broadcast from the owning lane with
 //     v_readlane into scalar registers, so each gathered B row is addressed
 //     by a scalar base plus the lane offset;
-//   * 4 to 8 gather instructions are in flight per wave;
+//   * 4 to 8 gather instructions are in flight per wave (16 in long rows of
+//     over 256 features);
 //   * products are accumulated in fp32 over each run of <= 64 entries and the
 //     run sum is folded into an fp64 accumulator; one fp32 rounding per output;
 //   * rows with more than kLongRow entries are taken by a whole block: the
@@ -52,7 +53,7 @@ constexpr int32_t kWideBlockRows = 16384;
 constexpr int32_t kWideBlockMean = 32;
 constexpr int kCoopWindow = 1024;      // blocks that share out the long rows among theirs
 constexpr int kSpmmLongBlocks = 1024;  // blocks that walk a long-row list of unknown length
-constexpr int kSpmmLongBlocksMax = 8192;  // blocks for a list of known length (one row each up to here), or to look for the rows
+constexpr int kSpmmLongBlocksMax = 8192;  // ... of known length (a row each up to here), or that look for them
 constexpr int32_t kListedRows = 262144;  // from here on an unplanned product lists its long rows
 static_assert(kListedRows <= kSpmmLongBlocksMax * kSpmmWaves * kWave, "a thread for each row that is looked at");
 
@@ -120,19 +121,34 @@ __global__ __launch_bounds__(kCollectThreads) void collect_long_rows_kernel(
 
 // ---- one entry per load instruction (LPE = 64) ----------------------------
 // Accumulates runs of 64 entries starting at beg, beg + stride, ... (< end)
-// into acc. `act[q]` says whether this lane's q-th float4 lies inside d.
+// into acc; d features, 4 a lane and vector q.
 // (col, val) are broadcast into SGPRs, so each B row has a scalar base.
 // Bit 31 of a column index is a cache hint (set by a plan or a cache on
 // their own copies; a caller's indices are < 2^31): with kHint, gathers of
 // columns without it bypass cache allocation (non-temporal), so the rows of
 // the columns that carry half the entries stay in L2. Values are unchanged.
-template <int NV, bool kHint>
+// kWin gathers are in flight. kAll: lanes past the last feature read the last
+// vector again in place of being masked (their sums are never stored). Without
+// the mask the two kinds of load are a uniform choice, where with it the
+// compiler waits for each gather before the next. A long row, whose waits no
+// other wave hides, takes a third of the time so (4,000 rows, one of 1,000,000
+// entries, d = 512, hinted: 80.7 ms / 27.5); short rows gain or lose by their
+// number and width (hinted, 1,500,000 rows of 3, d = 300: 1,641 us / 1,319;
+// 400,000 of 6, d = 512: 748 / 782) and are left masked.
+template <int NV, bool kHint, int kWin, bool kAll>
 __device__ __forceinline__ void accumulate_runs(const int32_t *__restrict__ col,
                                                 const float *__restrict__ val,
                                                 const float *__restrict__ B, int64_t ldb,
                                                 int64_t beg, int64_t end, int32_t stride,
-                                                const bool (&act)[NV], int lane,
-                                                double (&acc)[NV][4]) {
+                                                int32_t d, int lane, double (&acc)[NV][4]) {
+    bool act[NV];  // this lane's q-th float4 lies inside d
+    int32_t at[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        at[q] = lane + kWave * q;
+        act[q] = 4 * at[q] < d;
+        if (kAll) at[q] = min(at[q], (d - 1) / 4);
+    }
     for (int64_t base = beg; base < end; base += stride) {  // int64: base + stride may pass 2^31 - 1
         const int32_t cnt = __builtin_amdgcn_readfirstlane((int32_t)min<int64_t>(kWave, end - base));
         int32_t my_c = 0;
@@ -144,32 +160,36 @@ __device__ __forceinline__ void accumulate_runs(const int32_t *__restrict__ col,
         float a[NV][4];
 #pragma unroll
         for (int q = 0; q < NV; ++q) a[q][0] = a[q][1] = a[q][2] = a[q][3] = 0.f;
-        for (int32_t t = 0; t < cnt; t += kUnroll) {
-            float4 b[kUnroll][NV];
-            float v[kUnroll];
+        for (int32_t t = 0; t < cnt; t += kWin) {
+            float4 b[kWin][NV];
+            float v[kWin];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < kWin; ++u) {
+                if constexpr (!kAll) {
 #pragma unroll
-                for (int q = 0; q < NV; ++q) b[u][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    for (int q = 0; q < NV; ++q) b[u][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
                 v[u] = 0.f;
                 if (t + u < cnt) {  // wave-uniform
                     const int32_t cf = __builtin_amdgcn_readlane(my_c, t + u);
-                    const int32_t c = cf & kColMask;
                     v[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), t + u));
-                    const float4 *brow = reinterpret_cast<const float4 *>(B + (int64_t)c * ldb) + lane;
+                    const float4 *brow = reinterpret_cast<const float4 *>(B + (int64_t)(cf & kColMask) * ldb);
                     if (kHint && cf >= 0) {  // not a hub column: stream it past the caches
 #pragma unroll
                         for (int q = 0; q < NV; ++q)
-                            if (act[q]) b[u][q] = load_nt(brow + q * kWave);
+                            if (kAll || act[q]) b[u][q] = load_nt(brow + at[q]);
                     } else {
 #pragma unroll
                         for (int q = 0; q < NV; ++q)
-                            if (act[q]) b[u][q] = brow[q * kWave];
+                            if (kAll || act[q]) b[u][q] = brow[at[q]];
                     }
+                } else if constexpr (kAll) {
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) b[u][q] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u)
+            for (int u = 0; u < kWin; ++u)
 #pragma unroll
                 for (int q = 0; q < NV; ++q) {
                     a[q][0] = fmaf(v[u], b[u][q].x, a[q][0]);
@@ -352,14 +372,14 @@ __device__ __forceinline__ void accumulate_groups(const int32_t *__restrict__ co
 
 // The same sums with 64-bit addresses and a lane mask per step; kHint as in
 // accumulate_runs.
-template <int LPE, bool kHint>
+template <int LPE, bool kHint, int kMaxWin>
 __device__ __forceinline__ void accumulate_groups_wide(const int32_t *__restrict__ col,
                                                        const float *__restrict__ val, const float *__restrict__ B,
                                                        int64_t ldb, int64_t beg, int64_t end, int32_t stride,
                                                        bool act, int lane, double (&acc)[4], float (&last)[4]) {
     constexpr int G = kWave / LPE;
     constexpr int kSteps = kWave / G;           // steps that cover the 64-entry run
-    constexpr int kWin = G >= 8 ? 4 : kUnroll;  // steps per window (gathers in flight)
+    constexpr int kWin = G >= 8 ? 4 : std::min(kMaxWin, kUnroll);  // steps per window (gathers in flight)
     const int g = lane / LPE, sl = lane % LPE;
     for (int64_t base = beg; base < end; base += stride) {
         if (base > beg) fold(last, acc);
@@ -422,16 +442,13 @@ __device__ __forceinline__ void sum_groups(T (&a)[4]) {
 
 // What a wave accumulates for one row with either kind of layout; in the
 // sliced ones the last run's sums are left in `last`.
-template <int LPE, int NV, bool kHint, bool kBuf>
+template <int LPE, int NV, bool kHint, bool kBuf, int kWin = kUnroll, bool kLong = false>
 __device__ __forceinline__ void accumulate(const int32_t *__restrict__ col, const float *__restrict__ val,
                                            const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, int64_t beg,
                                            int64_t end, int32_t stride, int32_t d, int lane, double (&acc)[NV][4],
                                            float (&last)[4]) {
     if constexpr (LPE == kWave) {
-        bool act[NV];
-#pragma unroll
-        for (int q = 0; q < NV; ++q) act[q] = 4 * lane + 4 * kWave * q < d;
-        accumulate_runs<NV, kHint>(col, val, B, ldb, beg, end, stride, act, lane, acc);
+        accumulate_runs<NV, kHint, kWin, kLong>(col, val, B, ldb, beg, end, stride, d, lane, acc);
     } else {
         static_assert(NV == 1, "the sliced layouts hold one float4 per lane");
         if constexpr (kBuf) {
@@ -444,8 +461,8 @@ __device__ __forceinline__ void accumulate(const int32_t *__restrict__ col, cons
             if (beg < end)
                 accumulate_groups<LPE>(col, val, op, (uint32_t)(4 * ldb), beg, end, stride, lane, acc[0], last);
         } else {
-            accumulate_groups_wide<LPE, kHint>(col, val, B, ldb, beg, end, stride, 4 * (lane % LPE) < d, lane,
-                                               acc[0], last);
+            accumulate_groups_wide<LPE, kHint, kWin>(col, val, B, ldb, beg, end, stride, 4 * (lane % LPE) < d, lane,
+                                                     acc[0], last);
         }
     }
 }
@@ -466,8 +483,9 @@ __device__ __forceinline__ void store_row(float *__restrict__ yrow, int32_t d, i
 }
 
 // A long row by the whole block: the waves' sums are added in wave order
-// through LDS and the last wave stores the total. Reached by every wave.
-template <int LPE, int NV, bool kHint, bool kBuf, int kWaves>
+// through LDS and the last wave stores the total. Reached by every wave. kWin
+// gathers are in flight per wave (one entry per load).
+template <int LPE, int NV, bool kHint, bool kBuf, int kWaves, int kWin>
 __device__ __forceinline__ void take_long_row(const int32_t *__restrict__ col, const float *__restrict__ val,
                                               const float *__restrict__ B, int64_t ldb, uint32_t b_bytes,
                                               float *__restrict__ yrow, int32_t d, int32_t s, int32_t e, int lane,
@@ -476,8 +494,8 @@ __device__ __forceinline__ void take_long_row(const int32_t *__restrict__ col, c
 #pragma unroll
     for (int q = 0; q < NV; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.0;
     float last[4] = {0.f, 0.f, 0.f, 0.f};
-    accumulate<LPE, NV, kHint, kBuf>(col, val, B, ldb, b_bytes, (int64_t)s + kWave * wave, e, kWave * kWaves, d, lane,
-                                     acc, last);
+    accumulate<LPE, NV, kHint, kBuf, kWin, true>(col, val, B, ldb, b_bytes, (int64_t)s + kWave * wave, e,
+                                                 kWave * kWaves, d, lane, acc, last);
     if constexpr (LPE < kWave) fold(last, acc[0]);
     // opaque: what derives from the lane below is computed here and not kept
     // in registers through the gathers
@@ -517,48 +535,80 @@ __device__ __forceinline__ void take_long_row(const int32_t *__restrict__ col, c
 //     short rows are done. A window is about what the chip holds at once, so a
 //     long piece reads the range of B that its neighbours read.
 // (Blocks that took the long ones of their own rows: 60,013 rows, mean 27,
-// hubs of 30,000 entries in the first rows, d = 41: 426 us, against 131; d =
-// 128: 758, against 255.)
+// hubs of 30,000 entries in the first rows, d = 41: 426 us, against 129; d =
+// 128: 758, against 246.)
 // With `order`, the rows are taken in that order after its first *long_count
 // entries (the long rows). Which block takes a row never changes its sum.
 // (Long rows in a launch of their own before the others left the chip to its
-// last few rows twice, and cost a counter reset per pass. us, two launches /
-// one: 60,013 nodes, mean 27, d = 41, kCoop: 70 / 52; 716,847 nodes, mean 20,
-// d = 512: 4,160 / 4,044; the 30 % slice of 232,965 nodes, mean 490, d = 256:
-// 3,257 / 3,122.)
+// last few rows twice. us, two launches / one: 60,013 nodes, mean 27, d = 41
+// 70 / 46; 716,847 nodes, mean 20, d = 512: 4,160 / 4,044; the 30 % slice of
+// 232,965 nodes, mean 490, d = 256: 3,257 / 3,122.)
+//
+// A long row is a serial chain: with one entry per load, 4 waves have too few
+// gathers in flight. Its features are halved over two blocks then (kParts;
+// the n_long blocks are pairs), which have twice as many entries in flight:
+// over 256 features as 16 gathers of 1 KB in place of 8 of 2 KB, fewer in the
+// 128-float layout, two entries per load. 8-wave blocks take theirs whole. us,
+// whole with 4 waves / so: 60,013 rows, mean 27, hubs of 30,000 entries, d =
+// 256: 888 / 344; a row of 1,000,000 entries among 4,000, d = 256: 32,000 /
+// 9,300, d = 512: 40,800 / 24,000.
+constexpr int long_parts(int lpe, int nv, int waves) { return lpe == kWave && (nv == 2 || waves == 4) ? 2 : 1; }
+
 template <int LPE, int NV, bool kCsr, bool kHint, bool kBuf, bool kCoop, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) void spmm_kernel(
     const int32_t *__restrict__ ptr, int64_t off, const int32_t *__restrict__ col, const float *__restrict__ val,
     const float *__restrict__ B, int64_t ldb, uint32_t b_bytes, float *__restrict__ Y, int64_t ldy, int32_t n_rows,
     int32_t d, int32_t n_long, const int32_t *__restrict__ list, int32_t ordered,
     const int32_t *__restrict__ long_count) {
-    __shared__ double red[NV * 4][kWave];
+    __shared__ double red[4][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    constexpr int kParts = long_parts(LPE, NV, kWaves), kHalf = 2 * kWave * NV;  // of the features
     const auto take_long = [&](int32_t r) {
         const int32_t s = __builtin_amdgcn_readfirstlane(ptr[r]);
         const int32_t e = __builtin_amdgcn_readfirstlane(ptr[(int64_t)r + (kCsr ? 1 : off)]);
         int ln = lane;
         asm volatile("" : "+v"(ln));  // as in take_long_row
-        take_long_row<LPE, NV, kHint, kBuf, kWaves>(col, val, B, ldb, b_bytes, Y + (int64_t)r * ldy, d, s, e, ln,
-                                                    wave, red);
+        if constexpr (kParts == 1) {
+            take_long_row<LPE, 1, kHint, kBuf, kWaves, kUnroll>(col, val, B, ldb, b_bytes, Y + (int64_t)r * ldy, d, s, e,
+                                                                ln, wave, red);
+        } else {  // 6: the 64-bit form then keeps 64 registers, as the short rows do
+            const int32_t f = blockIdx.x % 2 * kHalf;
+            take_long_row<NV == 2 ? kWave : kWave / 2, 1, kHint, kBuf, kWaves, NV == 2 ? 2 * kUnroll : 6>(
+                col, val, B + f, ldb, b_bytes - 4 * f, Y + (int64_t)r * ldy + f, min(d - f, kHalf), s, e, ln, wave, red);
+        }
     };
     const int32_t bid = blockIdx.x;
     if constexpr (!kCoop) {
         if (bid < n_long) {
-            __shared__ int32_t found[kWaves * kWave];
-            __shared__ int32_t n_found;
-            if (!list) {  // n_long * kWaves * kWave >= n_rows
-                if (threadIdx.x == 0) n_found = 0;
-                __syncthreads();
-                const int32_t q = bid + n_long * threadIdx.x;
-                if (q < n_rows && ptr[q + 1] - ptr[q] > kLongRow) found[atomicAdd(&n_found, 1)] = q;
+            if (kParts == 2 && bid % 2 * kHalf >= d) return;
+            const int32_t me = bid / kParts, n_me = n_long / kParts;
+            __shared__ uint64_t found[kWaves];
+            if (!list) {  // thread t looks at row me + n_me t (n_me * kWaves * kWave >= n_rows)
+                const int32_t q = me + n_me * threadIdx.x;
+                const uint64_t mine = __ballot(q < n_rows && ptr[q + 1] - ptr[q] > kLongRow);
+                if (lane == 0) found[wave] = mine;
                 __syncthreads();
             }
-            const int32_t n_list = __builtin_amdgcn_readfirstlane(list ? *long_count : n_found);
-            for (int32_t j = list ? bid : 0; j < n_list; j += list ? n_long : 1)
-                take_long(__builtin_amdgcn_readfirstlane(list ? list[j] : found[j]));
-            return;
+            const int32_t n_list = list ? __builtin_amdgcn_readfirstlane(*long_count) : kWaves;
+            uint64_t left = 0;  // of the 64 rows that wave j looked at
+            for (int32_t j = list ? me : -1;;) {
+                int32_t r;
+                if (list) {
+                    if (j >= n_list) return;
+                    r = __builtin_amdgcn_readfirstlane(list[j]);
+                    j += n_me;
+                } else {
+                    while (left == 0) {
+                        if (++j == n_list) return;
+                        left = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(found[j] >> 32)) << 32 |
+                               (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)found[j]);
+                    }
+                    r = me + n_me * (j * kWave + __builtin_ctzll(left));
+                    left &= left - 1;
+                }
+                take_long(r);
+            }
         }
     }
     const int32_t first = (kCoop ? bid : bid - n_long) * kWaves;  // the block's first row
@@ -605,12 +655,13 @@ __global__ __launch_bounds__(kWaves * 64) void spmm_kernel(
                 sum_groups<LPE>(last[0]);
 #pragma unroll
                 for (int x = 0; x < 4; ++x) last[0][x] += 0.f;
-                store_row<LPE, 1>(Y + (int64_t)r * ldy, d, lane, last);
             } else {
                 fold(last[0], acc[0]);
                 sum_groups<LPE>(acc[0]);
-                store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) last[0][x] = (float)acc[0][x];
             }
+            store_row<LPE, 1>(Y + (int64_t)r * ldy, d, lane, last);
         } else {
             store_row<LPE, NV>(Y + (int64_t)r * ldy, d, lane, acc);
         }
@@ -1051,10 +1102,11 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
     for (int32_t f0 = 0; f0 < d;) {
         const int32_t dl = std::min<int32_t>(d - f0, slice);
         const uint32_t bb = buffer_bytes(n_cols, ldb, dl);
-#define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_, BUF_, W_)                                                     \
-    launch(spmm_kernel<LPE_, NV_, true, H_, BUF_, false, W_>, (unsigned)(n_long + ceil_div(n_rows, W_)), \
-           W_ * 64, stream, f0 + dl >= d ? stop : nullptr, rowptr, (int64_t)1, col, val, B + f0, ldb, bb, \
-           Y + f0, ldy, n_rows, dl, n_long, rows, (int32_t)(ordered ? 1 : 0), (const int32_t *)&h->long_count)
+#define RSC_SPMM_LAUNCH_H(LPE_, NV_, H_, BUF_, W_)                                                       \
+    launch(spmm_kernel<LPE_, NV_, true, H_, BUF_, false, W_>,                                            \
+           (unsigned)(long_parts(LPE_, NV_, W_) * n_long + ceil_div(n_rows, W_)), W_ * 64, stream,       \
+           f0 + dl >= d ? stop : nullptr, rowptr, (int64_t)1, col, val, B + f0, ldb, bb, Y + f0, ldy, n_rows, dl, \
+           long_parts(LPE_, NV_, W_) * n_long, rows, (int32_t)(ordered ? 1 : 0), (const int32_t *)&h->long_count)
 #define RSC_SPMM_LAUNCH_SLICED(LPE_)                                \
     do {                                                            \
         if (hint)                                                   \
@@ -1070,6 +1122,8 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
             RSC_SPMM_LAUNCH_H(64, 2, H_, false, kSpmmWaves);        \
         else if (wide_blocks)                                       \
             RSC_SPMM_LAUNCH_H(64, 1, H_, false, 8);                 \
+        else if (!H_ && bb != 0)                                    \
+            RSC_SPMM_LAUNCH_H(64, 1, false, true, kSpmmWaves);      \
         else                                                        \
             RSC_SPMM_LAUNCH_H(64, 1, H_, false, kSpmmWaves);        \
     } while (0)

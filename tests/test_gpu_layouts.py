@@ -126,6 +126,32 @@ def _side_by_side(n_rows, first, count, n_cols, seed):
     return synth.bucket_csr(lens, n_cols, seed=seed)
 
 
+@pytest.mark.parametrize("d", [130, 200, 256, 257, 300, 512, 600])
+def test_long_rows_halved(d):
+    """Long rows of 129 and more features, halved over two blocks: through a
+    descriptor, with 64-bit addresses (an operand of more than 4 GiB) and with
+    the hub hint (B over 512 MiB), the same bits; NaN in the B rows and
+    features that no entry or output uses."""
+    n_cols = 1_100_000
+    A = synth.bucket_csr(np.array([1024, 1025, 3, 1088, 5, 0, 2000, 64, 65, 1500, 1026]), n_cols - 2, seed=d)
+    col = A.col + 1
+    wide = torch.full((n_cols, 1024), float("nan"), device="cuda")
+    wide[1:-1, :d] = torch.randn((n_cols - 2, d), generator=torch.Generator("cuda").manual_seed(d), device="cuda")
+    B = wide[:, :(d + 3) // 4 * 4].contiguous()
+    X = rsc.DeviceCsr.from_host(A.rowptr, col, A.val, n_cols)
+    Y = rsc.spmm(X, B, d=d)
+    assert torch.equal(rsc.spmm(X, wide, d=d), Y)
+    plan = rsc.SpmmPlan(X)
+    assert torch.equal(plan.run(B, d=d), Y)
+    plan.close()
+    used = np.unique(col)
+    Bh = np.zeros((n_cols, d), np.float32)
+    Bh[used] = B[torch.from_numpy(used.astype(np.int64)).cuda(), :d].cpu().numpy()
+    Yo, S = oracle.spmm(A.rowptr, col, A.val, Bh, d=d, with_mag=True)
+    err = np.max(np.abs(Y.cpu().numpy().astype(np.float64) - Yo) / np.maximum(S, FLT_MIN))
+    assert err <= 66 * 2.0 ** -24   # a 64-entry fp32 chain at most, then fp64
+
+
 @pytest.mark.parametrize("n_rows,first,count", [
     (5000, 0, 600),              # more blocks look than there are groups of 256 rows
     (4099, 4000, 99),            # up to the last row
@@ -199,3 +225,27 @@ def test_sorted_hubs_cost_what_scattered_ones_cost(d):
             best = min(best, a.elapsed_time(b))
         times.append(best)
     assert times[0] <= 1.6 * times[1], times
+
+
+def test_one_long_row_costs_its_bytes():
+    """A row that outweighs all others is one block's serial chain: with four
+    times the features it may take little more than four times as long (nine
+    times, with the gathers of four waves in flight)."""
+    n_cols = 1_000_000
+    lens = np.full(1000, 4)
+    lens[500] = 300_000
+    A = synth.bucket_csr(lens, n_cols, seed=9)
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n_cols)
+    best = {}
+    for d in (64, 256):
+        B = torch.randn((n_cols, d), device="cuda")
+        Y = rsc.spmm(X, B)
+        best[d] = float("inf")
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            rsc.spmm(X, B, out=Y)
+            b.record()
+            b.synchronize()
+            best[d] = min(best[d], a.elapsed_time(b))
+    assert best[256] <= 5 * best[64], best
