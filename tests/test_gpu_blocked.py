@@ -2,8 +2,8 @@
 one after another, partial rows added in fixed range order). Forced with
 RSC_SPMM_BLOCKED = 2..8 on seeded random shapes, and chosen automatically on
 graphs whose B slice (16, 32 or 64 floats per row, by feature width) spans
-2 to 9 (capped to 8) and 17 (not blocked) L2-sized ranges, with plans and
-caches used at several widths: exact and sampled SpMM
+2 to 9 (capped to 8) and 17 (not blocked) L2-sized ranges, or 9 to 12 finer
+ones, with plans and caches used at several widths: exact and sampled SpMM
 against the oracle, a full-budget slice equal to the exact product bit for
 bit, and the automatic choice equal to the forced one."""
 import ctypes
@@ -182,8 +182,68 @@ def test_automatic_range_count(n_cols, d, row_len, P):
     assert rel_err(Y.cpu().numpy(), Yo, S) <= 1e-5
 
 
+@pytest.mark.parametrize("n_cols,d,row_len,P", [
+    (160_000, 64, 510, 9),     # 14 ranges of 3 MiB, 56 entries of a row in each of 9
+    (160_000, 96, 560, 10),
+    (130_000, 72, 700, 11),    # 11 ranges of 3 MiB
+    (160_000, 96, 1000, 12),   # 14, capped to 12
+])
+def test_finer_range_count(n_cols, d, row_len, P):
+    # More ranges than the switch forces; the count shows in the workspace,
+    # which holds the split bounds and partial rows of that many.
+    n_rows = 2000
+    A = synth.bucket_csr(np.full(n_rows, row_len), n_cols, seed=41)
+    AT = synth.transpose(A, n_cols)
+    B = synth.dense_normal(n_cols, d, seed=42)
+    Bd = torch.from_numpy(B).cuda()
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n_cols)
+    XT = rsc.DeviceCsr.from_host(AT.rowptr, AT.col, AT.val, n_rows)
+
+    def up(x):
+        return (x + 255) // 256 * 256
+
+    with blocked(None):
+        assert rsc.spmm_workspace_bytes(X) == 512 + up(4 * n_rows) + up(4 * n_rows * (P + 1)) + up(256 * P * n_rows)
+        Y = rsc.spmm(X, Bd)
+        plan = rsc.SpmmPlan(X)
+        Yp = plan.run(Bd)
+        plan.close()
+        cache = rsc.Cache(X, XT)
+        cache.refresh(Bd, n_cols, step=0)
+        Yk = cache.spmm_sampled(Bd)
+        cache.close()
+    with blocked(8):
+        Y8 = rsc.spmm(X, Bd)
+    assert torch.equal(Yp, Y) and torch.equal(Yk, Y)
+    assert not torch.equal(Y, Y8)
+    Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, with_mag=True)
+    # a group's fp32 chain of 16 entries and its tree, a rounding per range and one for the sum
+    assert rel_err(Y.cpu().numpy(), Yo, S) <= 24 * 2.0 ** -24
+    assert rel_err(Y8.cpu().numpy(), Yo, S) <= 24 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("d", [13, 16, 30, 32, 64, 100])
+def test_blocked_wide_addresses(d):
+    # An operand of more than 4 GiB between its first and last row is read
+    # with 64-bit addresses, long pieces among them: its compact copy's bits.
+    n_cols = 1_100_000
+    lens = np.array([0, 1, 63, 64, 65, 700, 1500, 4000, 3500, 2, 3200, 3100, 3300] * 9)
+    A = synth.bucket_csr(lens, n_cols, seed=43)
+    Bc = torch.from_numpy(synth.dense_normal(n_cols, (d + 3) // 4 * 4, seed=44)).cuda()
+    wide = torch.full((n_cols, 1024), float("nan"), device="cuda")
+    wide[:, :Bc.shape[1]] = Bc
+    X = rsc.DeviceCsr.from_host(A.rowptr, A.col, A.val, n_cols)
+    with blocked(3):
+        Y = rsc.spmm(X, Bc, d=d)
+        assert torch.equal(rsc.spmm(X, wide, d=d), Y)
+    with blocked(0):
+        assert not torch.equal(rsc.spmm(X, wide, d=d), Y)
+    Yo, S = oracle.spmm(A.rowptr, A.col, A.val, Bc.cpu().numpy(), d=d, with_mag=True)
+    assert rel_err(Y.cpu().numpy(), Yo, S) <= 24 * 2.0 ** -24
+
+
 def test_plan_and_cache_across_feature_widths():
-    # A plan prepares for 64-float passes (8 ranges here); a run at d = 16
+    # A plan prepares for 64-float passes (12 ranges here); a run at d = 16
     # takes 3 ranges (d = 32: 5) and prepares for itself, and later runs at
     # any width still equal rsc_spmm bit for bit. A cache refreshed at one
     # width and used at another does the same.
@@ -210,13 +270,13 @@ def test_plan_and_cache_across_feature_widths():
 
 
 @pytest.mark.parametrize("n_rows,n_cols,row_len,d", [
-    (100, 40_000, 10_000, 96),     # P = 3: 300 long pieces from 100 rows
+    (100, 40_000, 10_000, 96),     # P = 4: 400 long pieces from 100 rows
     (20_000, 20_000, 2_200, 64),   # P = 2: 40,000 pieces of 1,100 entries from 20,000 rows
 ])
 def test_long_pieces_outnumber_rows(n_rows, n_cols, row_len, d):
-    # Regression: the long-piece list of the column-blocked mode must hold up
-    # to P pieces per row (not one per row) when rows average over 1,024
-    # entries per range. The automatic rule picks the blocked mode here.
+    # Rows that average over 1,024 entries per range have up to P long pieces
+    # each, all of which the blocks of a window must find and share out. The
+    # automatic rule picks the blocked mode here.
     A = synth.bucket_csr(np.full(n_rows, row_len), n_cols, seed=21)
     B = synth.dense_normal(n_cols, d, seed=22)
     Bd = torch.from_numpy(B).cuda()
@@ -230,7 +290,7 @@ def test_long_pieces_outnumber_rows(n_rows, n_cols, row_len, d):
         Yu = rsc.spmm(X, Bd)
     torch.cuda.synchronize()
     assert not torch.equal(Y, Yu)              # the blocked mode ran (different partial rounding)
-    assert torch.equal(Y, Yp)                  # the plan's prepared list gives the same product
+    assert torch.equal(Y, Yp)                  # the plan's prepared split bounds give the same product
     Yo, S = oracle.spmm(A.rowptr, A.col, A.val, B, with_mag=True)
     assert rel_err(Y.cpu().numpy(), Yo, S) <= 1e-5
     assert rel_err(Yu.cpu().numpy(), Yo, S) <= 1e-5

@@ -58,7 +58,7 @@ def test_graph_replays_match_eager(name, d):
 
 def test_graph_replays_blocked_mode():
     """The column-blocked SpMM (forced to 4 ranges) captured and replayed:
-    split, long-piece list, row and combine kernels, all launch-only."""
+    split, row and combine kernels, all launch-only."""
     import os
     old = os.environ.get("RSC_SPMM_BLOCKED")
     os.environ["RSC_SPMM_BLOCKED"] = "4"

@@ -3,6 +3,7 @@ thread block, counts added tile by tile or by groups of tiles, the small
 forms, and searches that end before the last digit. Bit for bit against torch
 or the oracle; everything here is integer or copied."""
 import ctypes
+import math
 
 import numpy as np
 import pytest
@@ -106,13 +107,36 @@ def test_slice_of_mostly_empty_rows(n_rows, launches):
 @pytest.mark.parametrize("n,d", [(1, 4), (63, 100), (65, 64), (64, 65), (65_536, 96), (65_536, 100), (65_537, 100), (70_001, 64)])
 def test_scores_rows_per_block(n, d):
     """Keys and row norms over both block sizes and both load policies, bit
-    for bit; the norm's total against the sequential sum within (n - 1) u."""
+    for bit."""
     ld = (d + 3) // 4 * 4
     B = synth.dense_normal(n, d, seed=n, ld=ld)
     cn2 = np.random.default_rng(n).random(n)
     key, rn2 = rsc.pair_scores(torch.from_numpy(cn2).cuda(), torch.from_numpy(B).cuda(), d=d, with_rn2=True)
     want = oracle.pair_keys(cn2, B, d=d)
     assert np.array_equal(key.cpu().numpy().view(np.uint64), want["key"])
+    assert np.array_equal(rn2.cpu().numpy().view(np.uint64), want["rn2"].view(np.uint64))
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 8191, 8192, 8193, 16_384, 16_385])
+def test_norm_totals(n):
+    """The norms' totals over one block of 8,192 terms, which is stored by
+    itself, and over several: within (n - 1) u of the exact sum, twice the
+    same bits."""
+    val = np.random.default_rng(n).standard_normal(n).astype(np.float32)
+    X = rsc.DeviceCsr.from_host(np.arange(n + 1), np.arange(n), val, n)
+    B = synth.dense_normal(n, 8, seed=n)
+    cache = rsc.Cache(X, X)
+    Bd = torch.from_numpy(B).cuda()
+    cache.score(Bd)
+    totals = cache.norms()
+    rn2 = oracle.pair_keys(val.astype(np.float64) ** 2, B)["rn2"]
+    for got, terms in zip(totals, (val.astype(np.float64) ** 2, rn2)):
+        want = math.fsum(terms)
+        # (n - 1) roundings of the sum, and one of the exact sum
+        assert abs(got - want) <= n * 2.0 ** -53 * want, n
+    cache.score(Bd)
+    assert cache.norms() == totals
+    cache.close()
 
 
 def test_previous_selection_is_kept():

@@ -58,7 +58,7 @@ def test_consecutive_calls_match_rsc_spmm():
 
 
 def test_blocked_product_in_scratch_and_unblocked_fallback():
-    # 100 rows x 10,000 entries over 40,000 columns: rsc_spmm takes 3 column
+    # 100 rows x 10,000 entries over 40,000 columns: rsc_spmm takes 4 column
     # ranges, whose buffers fit the static scratch -> bitwise equal
     A, B = _case(np.full(100, 10_000), 40_000, 96, 31)
     Yn, Yw = _both(A, B, 40_000)
