@@ -153,8 +153,9 @@ rsc_status_t rsc_spmm_noalloc(const rsc_csr_t *A, const float *B, int32_t d, int
  *   - when the product runs column-blocked, the split bounds of the rows
  *     (for the range count of feature widths above 32; a run at a width
  *     whose range count differs builds its own, as rsc_spmm does);
- *   - the long-row list (or the length-class row order) and its length,
- *     which every rsc_spmm call builds first;
+ *   - the long-row list (or the length-class row order) and its length.
+ *     rsc_spmm builds the order, and the list from 262,144 rows on, in each
+ *     call; on fewer rows its first blocks look for the long rows themselves;
  *   - for operands with more than 262,144 columns, a copy of col whose bit
  *     31 marks the "hub" columns, the columns of highest entry count that
  *     together hold just under half of the entries (entry-weighted median of
@@ -339,7 +340,12 @@ rsc_status_t rsc_sample_columns(const uint64_t *key, int32_t n, int32_t k, uint6
  *     rsc_spmm; every row of Y' is written. Needs a refreshed cache. Each
  *     selection prepares the products for the feature width of the operand
  *     last scored (row list, or split bounds when column-blocked); a
- *     product of another width whose preparation differs builds its own. */
+ *     product of another width whose preparation differs builds its own.
+ *     One captured into a HIP graph holds the decisions of its capture and
+ *     reads the slice and its preparation when replayed: replays stay valid
+ *     over refreshes of the same k with an operand of the same width, as long
+ *     as no product of another width runs on the cache in between; capture
+ *     it again after any other. */
 typedef struct rsc_cache rsc_cache_t;
 rsc_status_t rsc_cache_create(const rsc_csr_t *X, const rsc_csr_t *XT, int32_t refresh_interval,
                               hipStream_t stream, rsc_cache_t **out);

@@ -816,20 +816,24 @@ inline size_t blocked_bytes(int32_t n_rows, int32_t P) {
 // are long enough that each piece still fills about 14 load instructions on
 // average: kPieceMin entries in the 64-float layout (4 entries per
 // instruction), twice and four times that in the 32- and 16-float layouts
-// (8 and 16 per instruction; shorter pieces made a power-law graph with
-// 489 entries per row slower at d = 16 and 32, while a uniform one with
-// 600 per row gained 16-33 %). Beyond 8 ranges P stays 8: ranges of up to
-// two L2 sizes still keep most gathers on chip (on a 233K-node graph with
-// 489 entries per row, 8 ranges of 7.5 MB measured 5 % faster than
-// unblocked passes at d = 256, while 32-float passes over ranges that do
-// fit L2 were slower: twice the passes over the row structure).
-// 64-float passes over long rows take ranges of 3 MiB instead, up to 12 of
-// them while a piece keeps kPieceMin entries: a range of 4.24 MB does not
-// quite fit an L2 that col, val and the partial rows stream through as well
-// (132,534 nodes, 600 entries per row, d = 256: 14 % of the gathers missed;
-// 4.68 ms with 8 ranges, 4.53 with 10, 4.49 with 12 of 50 entries each, 4.73
-// with 16). The narrower layouts and shorter rows lose by it (30 % of that
-// graph's columns: 1.53 ms with 3 ranges, 1.61 with 4). Where the scratch of
+// (8 and 16 per instruction). Beyond 8 ranges P stays 8: ranges of up to two
+// L2 sizes still keep most gathers on chip. 64-float passes over long rows
+// take ranges of 3 MiB instead, up to 12 of them while a piece keeps
+// kPieceMin entries: a range of 4.24 MB does not quite fit an L2 that col,
+// val and the partial rows stream through as well. Shorter rows lose by it.
+// us, by the number of ranges (1 = not blocked, * = the rule's):
+//   132,534 nodes, 600 per row, uniform
+//     d = 256, exact      1 9,508  6 4,823  8 4,640  10* 4,499  12 4,485  16 4,734
+//     30 % of the columns 1 1,600  2 1,498  3* 1,389  4 1,409  6 1,557
+//     d = 32, exact       1 1,175  3 682  4* 660  5 655  8 687
+//     d = 16, exact       1 827  2* 603  3 587  4 597  8 635
+//   232,965 nodes, 490 per row, power law
+//     d = 256, exact      1 9,279  4 7,634  6 7,360  8* 7,482  10 7,701  16 8,632
+//     30 % of the columns 1* 3,226  2 3,529  4 3,644  8 4,281
+//     d = 32, exact       1* 1,107  3 1,037  8 1,123; d = 16: 1* 957  4 908  8 1,021
+//   100,000 nodes, 260 per row, power law
+//     d = 256, exact      1* 1,835  2 1,904  4 1,842  8 2,054
+// Where the scratch of
 // rsc_spmm_noalloc holds the buffers of the 4.5 MiB ranges, no more ranges
 // than it holds, so that both calls give the same bits.
 // RSC_SPMM_BLOCKED=0 switches the mode off, =2..8 forces that P.
@@ -1037,7 +1041,7 @@ hipError_t spmm_launch(int32_t n_rows, int32_t n_cols, int64_t nnz_bound, const 
         // Long pieces (a piece of a row longer than kLongRow) are taken by
         // the block that holds them, so that they read the same range of B as
         // their neighbours (from a list, ahead of all ranges: 232,965 nodes,
-        // 490 per row, d = 256: 8.75 ms against 7.66).
+        // 490 per row, d = 256: 8.75 ms against 7.53).
         const int32_t coop = long_rows_bound(n_rows, nnz_bound) > 0 && !(pre && prep->long_rows == 0) ? 1 : 0;
         const unsigned vgrid = (unsigned)ceil_div(nv, kSpmmWaves);
         // partial rows are W floats apart (the workspace holds kBlockW)
